@@ -324,7 +324,7 @@ bool fifth_scan(int Ls, double M5, double m, double b, double c, int slot, Fifth
     FifthChir<double> q{};
     const int dS = ch == 0 ? -1 : +1;  // direction S~ takes in this chirality; the adjoint takes -dS
     q.a1 = 1.0; q.b1 = 0.0; q.d1 = dS; q.has_inv = 0; q.d2 = dS;
-    q.inv_alpha = 1.0 / alpha; q.a = a; q.corr = m / den;
+    q.inv_alpha = 1.0 / alpha; q.a = a; q.corr = m / den; q.inv_den = 1.0 / den;
     switch (slot) {
       case E_A: q.a1 = alpha; q.b1 = beta; q.d1 = dS; break;
       case E_ADAG: q.a1 = alpha; q.b1 = beta; q.d1 = -dS; break;

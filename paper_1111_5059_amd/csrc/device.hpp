@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_fp16.h>
 #include <stdint.h>
+#include <type_traits>
 
 namespace dwf {
 
@@ -260,6 +261,7 @@ struct FifthChir {
   R a1, b1;           // bidiagonal factor; b1 == 0: scalar
   R inv_alpha, a;     // inverse of (alpha + beta S_d2): 1/alpha and a = -beta/alpha
   R corr;             // m / (1 + m a^Ls)
+  R inv_den;          // 1 / (1 + m a^Ls)
   int d1, d2;         // shift directions (-1 or +1)
   int has_inv;
 };
@@ -269,24 +271,121 @@ struct FifthScan {
   R m;
 };
 
-// Apply the operator to the 12 components v[] held by this lane (slice s) when the Ls
-// lanes of a site are the consecutive lanes [seg*Ls, seg*Ls + Ls) of one wave.  The
-// inverse of (alpha + beta S_d) is the first-order recurrence y_s = u_s + a y_{s-+1},
-// u = w/alpha: a Hillis-Steele scan over the segment (log2 Ls shuffle steps) with zero
-// start, then the cyclic boundary y_{-1} = -m y_{Ls-1} (resp. y_{Ls} = -m y_0) is
-// restored in closed form:  y_s = P_s - m a^{s+1} P_{Ls-1} / (1 + m a^Ls)  (forward)
-// or y_s = Q_s - m a^{Ls-s} Q_0 / (1 + m a^Ls)  (backward).
+// Site-local operators along s on the 12 components held by this lane (slice s) when the LSEG
+// lanes of a site are the consecutive lanes [seg LSEG, (seg + 1) LSEG) of one wave.
+//
+// The inverse of (alpha + beta S_d) is that of (1 - a S_d), times 1/alpha.  With the cyclic
+// boundary S_d^LSEG = -m it is exactly
+//   (1 - a S)^-1 = (1 + a S)(1 + a^2 S^2)(1 + a^4 S^4) ... / (1 + m a^LSEG):
+// log2 LSEG steps v += c v_{s -+ off}, each a rotation of the segment with the per-lane
+// coefficient c = a^off, or -m a^off where the rotation wraps.  In FP32 a segment of 16 lanes
+// is one DPP row, and a step is one v_fmac_f32 with a rotated operand per value: no LDS-pipe
+// traffic, no selects and no separate pass for the boundary.  A segment of 32 lanes is two rows:
+// a scan with zero start inside each row (row shifts that read 0 beyond the row), then the two
+// rows' carries, which only need the rows' last (first) values, in closed form.  Other segments
+// and FP64 rotate with ds_bpermute (one rotation and one fma per step and value).
+// What it replaced, a zero-start scan with a select per step and a separate boundary pass, cost
+// 144 ds_bpermute and about 340 VALU instructions per lane.  The FP16 hops with this epilogue at
+// 24^3 x 64, Ls = 32 went from 676 to 599 us, those with two of them from 920 to 752 us; FP32,
+// Ls = 16: 615 to 570 and 725 to 640 us.
+// (The fmac steps are inline asm because the compiler emits a DPP move and a separate fma.  Each
+// block starts with the five wait states that DPP needs after an EXEC or operand write; inside a
+// block a value is read again only twelve instructions after it was written.)
 template <int LSEG, typename R>
 __device__ __forceinline__ R seg_shfl(R v, int src) {
   return __shfl(v, src, LSEG);
 }
 
+#define DWF_DPP12(CTRL, COEF)                                                                      \
+  "v_fmac_f32_dpp %0, %0, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
+  "v_fmac_f32_dpp %1, %1, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
+  "v_fmac_f32_dpp %2, %2, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
+  "v_fmac_f32_dpp %3, %3, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
+  "v_fmac_f32_dpp %4, %4, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
+  "v_fmac_f32_dpp %5, %5, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
+  "v_fmac_f32_dpp %6, %6, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
+  "v_fmac_f32_dpp %7, %7, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
+  "v_fmac_f32_dpp %8, %8, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
+  "v_fmac_f32_dpp %9, %9, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
+  "v_fmac_f32_dpp %10, %10, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"           \
+  "v_fmac_f32_dpp %11, %11, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
+#define DWF_DPP_SCAN(C1, C2, C4, C8)                                                               \
+  asm("s_nop 4\n" DWF_DPP12(C1, "%12") DWF_DPP12(C2, "%13") DWF_DPP12(C4, "%14") DWF_DPP12(C8, "%15") \
+      : "+v"(v[0].re), "+v"(v[0].im), "+v"(v[1].re), "+v"(v[1].im), "+v"(v[2].re), "+v"(v[2].im), "+v"(v[3].re), \
+        "+v"(v[3].im), "+v"(v[4].re), "+v"(v[4].im), "+v"(v[5].re), "+v"(v[5].im)                  \
+      : "v"(c1), "v"(c2), "v"(c4), "v"(c8))
+
+// four steps on six components: rotations of the 16-lane row (from s - off, BACK from s + off),
+// or shifts that read 0 beyond it
+template <bool BACK>
+__device__ __forceinline__ void row_rotate_steps(cx<float>* v, float c1, float c2, float c4, float c8) {
+  if constexpr (BACK) DWF_DPP_SCAN("row_ror:15", "row_ror:14", "row_ror:12", "row_ror:8");
+  else DWF_DPP_SCAN("row_ror:1", "row_ror:2", "row_ror:4", "row_ror:8");
+}
+template <bool BACK>
+__device__ __forceinline__ void row_shift_steps(cx<float>* v, float c1, float c2, float c4, float c8) {
+  if constexpr (BACK) DWF_DPP_SCAN("row_shl:1", "row_shl:2", "row_shl:4", "row_shl:8");
+  else DWF_DPP_SCAN("row_shr:1", "row_shr:2", "row_shr:4", "row_shr:8");
+}
+// the value of lane LANE of this lane's group of 32
+template <int LANE>
+__device__ __forceinline__ float bcast32(float v) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), LANE << 5));
+}
+
+// (1 - a S_d)^-1 (1 + m a^LSEG) on six components (32 lanes: (1 - a S_d)^-1)
+template <int LSEG, bool BACK, typename R>
+__device__ __forceinline__ void seg_inverse(cx<R>* v, int s, const FifthChir<R>& c, R m) {
+  if constexpr (std::is_same<R, float>::value && LSEG == 16) {
+    const R a2 = c.a * c.a, a4 = a2 * a2, a8 = a4 * a4;
+    const int d = BACK ? 15 - s : s;  // slices before the wrap
+    row_rotate_steps<BACK>(v, d >= 1 ? c.a : -m * c.a, d >= 2 ? a2 : -m * a2, d >= 4 ? a4 : -m * a4,
+                           d >= 8 ? a8 : -m * a8);
+  } else if constexpr (std::is_same<R, float>::value && LSEG == 32) {
+    const R a2 = c.a * c.a, a4 = a2 * a2, a8 = a4 * a4, a16 = a8 * a8;
+    row_shift_steps<BACK>(v, c.a, a2, a4, a8);
+    // carries: c0 enters the row that holds the wrap, c1 the other; with n, f the near and far
+    // rows' end values (the row entered first is the far one's successor across the wrap)
+    //   c0 = -m (f + a^16 n) / den,  c1 = (n - m a^16 f) / den,  den = 1 + m a^32
+    const int i = BACK ? 15 - (s & 15) : s & 15;
+    R w = c.a;  // a^{i+1}
+    w *= (i & 1) ? c.a : R(1);
+    w *= (i & 2) ? a2 : R(1);
+    w *= (i & 4) ? a4 : R(1);
+    w *= (i & 8) ? a8 : R(1);
+    const bool first = BACK ? s >= 16 : s < 16;
+    const R wm = -w * c.corr;  // corr = m / den
+    const R kn = first ? wm * a16 : w * c.inv_den, kf = first ? wm : wm * a16;
+#pragma unroll
+    for (int k = 0; k < 6; ++k) {
+      const R nr = bcast32<BACK ? 16 : 15>(v[k].re), ni = bcast32<BACK ? 16 : 15>(v[k].im);
+      const R fr = bcast32<BACK ? 0 : 31>(v[k].re), fi = bcast32<BACK ? 0 : 31>(v[k].im);
+      v[k] = {fma(kf, fr, fma(kn, nr, v[k].re)), fma(kf, fi, fma(kn, ni, v[k].im))};
+    }
+  } else {
+    R ap = c.a;
+#pragma unroll
+    for (int off = 1; off < LSEG; off <<= 1) {
+      const int src = BACK ? s + off : s - off;
+      const R f = (src < 0 || src >= LSEG) ? -m * ap : ap;
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        const R tr = seg_shfl<LSEG>(v[k].re, src & (LSEG - 1)), ti = seg_shfl<LSEG>(v[k].im, src & (LSEG - 1));
+        v[k] = {fma(f, tr, v[k].re), fma(f, ti, v[k].im)};
+      }
+      ap *= ap;
+    }
+  }
+}
+
+// the bidiagonal factors of an operator (operators without an inverse: all of it)
+// (one path with a run-time source lane: a DPP path per direction raised the fused CG hop from
+// 110 to 128 registers and spilled)
 template <int LSEG, typename R>
-__device__ __forceinline__ void fifth_scan_apply(cx<R> v[12], int s, const FifthScan<R>& e) {
+__device__ __forceinline__ void fifth_bidiagonal_apply(cx<R> v[12], int s, const FifthScan<R>& e) {
 #pragma unroll
   for (int ch = 0; ch < 2; ++ch) {
     const FifthChir<R> c = e.ch[ch];
-    // bidiagonal factor
     if (c.b1 != R(0)) {
       const int src = (s + c.d1) & (LSEG - 1);
       const bool wrap = (c.d1 < 0) ? (s == 0) : (s == LSEG - 1);
@@ -300,56 +399,22 @@ __device__ __forceinline__ void fifth_scan_apply(cx<R> v[12], int s, const Fifth
 #pragma unroll
       for (int k = ch * 6; k < ch * 6 + 6; ++k) v[k] = c.a1 * v[k];
     }
-    if (!c.has_inv) continue;
-    // inverse of the bidiagonal (alpha + beta S_d2)
+  }
+}
+
+template <int LSEG, typename R>
+__device__ __forceinline__ void fifth_scan_apply(cx<R> v[12], int s, const FifthScan<R>& e) {
+  fifth_bidiagonal_apply<LSEG>(v, s, e);
 #pragma unroll
-    for (int k = ch * 6; k < ch * 6 + 6; ++k) v[k] = c.inv_alpha * v[k];
-    R apow = c.a;
-    if (c.d2 < 0) {
+  for (int ch = 0; ch < 2; ++ch) {
+    const FifthChir<R> c = e.ch[ch];
+    if (!__builtin_amdgcn_readfirstlane(c.has_inv)) continue;
+    cx<R>* vc = v + ch * 6;
+    const R u = (std::is_same<R, float>::value && LSEG == 32) ? c.inv_alpha : c.inv_alpha * c.inv_den;
 #pragma unroll
-      for (int off = 1; off < LSEG; off <<= 1) {
-#pragma unroll
-        for (int k = ch * 6; k < ch * 6 + 6; ++k) {
-          const R tr = __shfl_up(v[k].re, off, LSEG), ti = __shfl_up(v[k].im, off, LSEG);
-          if (s >= off) v[k] = {v[k].re + apow * tr, v[k].im + apow * ti};
-        }
-        apow *= apow;
-      }
-      // a^{s+1}
-      R as = R(1), base = c.a;
-      for (int e2 = s + 1; e2; e2 >>= 1) {
-        if (e2 & 1) as *= base;
-        base *= base;
-      }
-      const R w = -c.corr * as;
-#pragma unroll
-      for (int k = ch * 6; k < ch * 6 + 6; ++k) {
-        const R lr = seg_shfl<LSEG>(v[k].re, LSEG - 1), li = seg_shfl<LSEG>(v[k].im, LSEG - 1);
-        v[k] = {v[k].re + w * lr, v[k].im + w * li};
-      }
-    } else {
-#pragma unroll
-      for (int off = 1; off < LSEG; off <<= 1) {
-#pragma unroll
-        for (int k = ch * 6; k < ch * 6 + 6; ++k) {
-          const R tr = __shfl_down(v[k].re, off, LSEG), ti = __shfl_down(v[k].im, off, LSEG);
-          if (s + off < LSEG) v[k] = {v[k].re + apow * tr, v[k].im + apow * ti};
-        }
-        apow *= apow;
-      }
-      // a^{Ls-s}
-      R as = R(1), base = c.a;
-      for (int e2 = LSEG - s; e2; e2 >>= 1) {
-        if (e2 & 1) as *= base;
-        base *= base;
-      }
-      const R w = -c.corr * as;
-#pragma unroll
-      for (int k = ch * 6; k < ch * 6 + 6; ++k) {
-        const R fr = seg_shfl<LSEG>(v[k].re, 0), fi = seg_shfl<LSEG>(v[k].im, 0);
-        v[k] = {v[k].re + w * fr, v[k].im + w * fi};
-      }
-    }
+    for (int k = 0; k < 6; ++k) vc[k] = u * vc[k];
+    if (__builtin_amdgcn_readfirstlane(c.d2) < 0) seg_inverse<LSEG, false, R>(vc, s, c, e.m);
+    else seg_inverse<LSEG, true, R>(vc, s, c, e.m);
   }
 }
 

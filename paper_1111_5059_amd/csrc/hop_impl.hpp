@@ -660,12 +660,13 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
       }
     }
   }
-  // the axpy operand given through a site-local operator (x_es2): es2 applied along the site's
-  // segment right after the read (every lane of a site is active or inactive together, so the
+  // the axpy operand given through a bidiagonal site-local operator (x_es2): es2 applied along
+  // the site's segment right after the read (every lane of a site is active or inactive together, so the
   // segment's shuffles read active lanes only)
   constexpr bool XS = CG && NS == 1 && RS == 0 && !ST && !std::is_same<P, P64>::value && (LS == 8 || LS == 16 || LS == 32);
   constexpr bool XSI = CG && RS > 0 && EPI < 2 && !std::is_same<P, P64>::value;  // per right-hand side
   double nrm = 0.0;
+  if constexpr (XS) __builtin_amdgcn_sched_barrier(0);  // (the operand's loads stay below the gathers: 128 -> 108 VGPRs)
   if (active) {
     const R alpha = CG ? R(a.cg_scalars[rhs * S_COUNT + S_ALPHA]) : R(0);
 #pragma unroll
@@ -675,9 +676,9 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
         cx<R> xv[12];
         load_spinor<P>(a.x, x, s, Ls, xv);
         if constexpr (XS) {
-          if (a.x_es2) fifth_scan_apply<(LS > 0 ? LS : 1)>(xv, s, a.es2);
+          if (a.x_es2) fifth_bidiagonal_apply<(LS > 0 ? LS : 1)>(xv, s, a.es2);
         } else if constexpr (XSI) {
-          if (a.x_es2) fifth_scan_apply<(RS > 0 ? RS : 1)>(xv, sr, es_lds[0][rhs]);
+          if (a.x_es2) fifth_bidiagonal_apply<(RS > 0 ? RS : 1)>(xv, sr, es_lds[0][rhs]);
         }
 #pragma unroll
         for (int k = 0; k < 12; ++k) acc[j][k] = acc[j][k] + a.ax * xv[k];
@@ -959,6 +960,7 @@ int launch_hop(const HopArgs<P>& a, bool dagger, bool prologue, const LaunchCfg&
   // lane, the site's Ls lanes a wave segment)
   const bool seg_shape = cfg.ns == 1 && (a.Ls == 8 || a.Ls == 16 || a.Ls == 32);
   if (a.x_es2 && (!a.cg_r.data || !a.x.data || !x_es2_shape<P>(cfg, a.Ls) || batch)) return -1;
+  if (a.x_es2 && (a.es2.ch[0].has_inv || a.es2.ch[1].has_inv)) return -1;  // (bidiagonal operators only)
   if (!a.cg_r.data && !a.out.data && !(a.out2.data && a.E && a.epi_scan && seg_shape)) return -1;
   const int threads = cfg.spb * (a.Ls / cfg.ns);
   if (threads > 256) return -1;

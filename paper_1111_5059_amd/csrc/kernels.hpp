@@ -44,7 +44,7 @@ struct HopArgs {
   CHalf<P> x;                  // axpy operand (data == nullptr: none)
   typename P::R ax;
   // x_es2 != 0 (fused CG step, scan epilogue shapes only): the axpy operand is es2 . x, the
-  // site-local operator applied to x in registers (the CG hop then reads A^-dag q, which it
+  // bidiagonal site-local operator applied to x in registers (the CG hop then reads A^-dag q, which it
   // turns back into q = A^dag (A^-dag q), and q itself need not be stored); interleaved right-
   // hand sides take the operator of each from es2_tab
   int x_es2 = 0;

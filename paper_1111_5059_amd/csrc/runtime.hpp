@@ -193,7 +193,7 @@ struct Op {
       es[slot].m = R(e.m);
       for (int ch = 0; ch < 2; ++ch) {
         const FifthChir<double>& q = e.ch[ch];
-        es[slot].ch[ch] = FifthChir<R>{R(q.a1), R(q.b1), R(q.inv_alpha), R(q.a), R(q.corr), q.d1, q.d2, q.has_inv};
+        es[slot].ch[ch] = FifthChir<R>{R(q.a1), R(q.b1), R(q.inv_alpha), R(q.a), R(q.corr), R(q.inv_den), q.d1, q.d2, q.has_inv};
       }
     }
   }

@@ -1,0 +1,38 @@
+"""Kernel paths chosen by size, precision and fifth-dimension extent, against the oracle at the edges
+of their ranges.  Tolerances are those of one application in the storage precision (FP64 1e-12,
+FP32 1e-5, FP16 4e-3, BF16 3e-2 of the largest component), as for every operator test here."""
+import numpy as np
+import pytest
+
+import synth
+from gpu_helpers import PREC_TOL, gpu_ctx, mask, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def env():
+    return gpu_ctx()
+
+
+@pytest.mark.parametrize("Ls", [8, 16, 32])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("mass,M5", [(1.0, 1.8), (0.3, 3.9)])
+def test_cyclic_recurrence(env, ora, Ls, prec, mass, M5):
+    """A^-1 and A^-dag where the boundary counts most: mass 1, and M5 = 3.9, where the recurrence's
+    factor is 1 / 1.1 and its powers reach across the whole segment (one row of lanes, half a row
+    or two)."""
+    dwf, ctx = env
+    P = dwf.PREC_NAMES[prec]
+    dims = (4, 2, 2, 6)
+    psi = mask(synth.gaussian_spinor(dims, Ls, 860 + Ls), dims, 0)
+    lat = dwf.Lattice(ctx, dims, Ls, M5=M5, mass=mass)
+    po = ora.params(dims, Ls, M5=M5, mass=mass)
+    U = lat.pack_gauge(synth.random_links(dims, 0.5, 861), P)
+    src = lat.pack(psi, dwf.KIND_EVEN, P)
+    for dag in (False, True):
+        dst = lat.empty(dwf.KIND_EVEN, P)
+        dwf.dwf_dslash(ctx, lat.params(P), U, src, dst, dwf.OP_AINV, 0, dag)
+        ref = mask(ora.fifth(po, psi, "Ainv" + ("dag" if dag else "")), dims, 0)
+        err = rel_err(lat.unpack_np(dst, dwf.KIND_EVEN, P), ref)
+        assert err < PREC_TOL[prec], (dag, err)
