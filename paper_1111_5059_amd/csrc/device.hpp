@@ -132,15 +132,37 @@ __host__ __device__ inline CHalf<P> chalf_view(const void* base, long nsites, in
   return {h.data, h.norm};
 }
 
-// Load the 12 complex components of 5D site (x, s)
-template <typename P>
+// one element read or written, optionally with the non-temporal hint
+template <typename T>
+struct nt_type { typedef T type; };
+template <>
+struct nt_type<double2> { typedef double type __attribute__((ext_vector_type(2))); };
+template <>
+struct nt_type<float2> { typedef float type __attribute__((ext_vector_type(2))); };
+template <>
+struct nt_type<__half2> { typedef uint32_t type; };
+template <bool NT, typename T>
+__device__ __forceinline__ T get(const T* p) {
+  if constexpr (!NT) return *p;
+  typedef typename nt_type<T>::type V;
+  return __builtin_bit_cast(T, __builtin_nontemporal_load(reinterpret_cast<const V*>(p)));
+}
+template <bool NT, typename T>
+__device__ __forceinline__ void put(T* p, const T& v) {
+  typedef typename nt_type<T>::type V;
+  if constexpr (NT) __builtin_nontemporal_store(__builtin_bit_cast(V, v), reinterpret_cast<V*>(p));
+  else *p = v;
+}
+
+// Load the 12 complex components of 5D site (x, s) (NT: see store_spinor)
+template <typename P, bool NT = false>
 __device__ __forceinline__ void load_spinor(CHalf<P> f, long x, int s, int Ls, cx<typename P::R> v[12]) {
   using R = typename P::R;
   const typename P::S* p = f.data + size_t(x) * 12 * Ls + s;
 #pragma unroll
-  for (int k = 0; k < 12; ++k) v[k] = P::ld(p[k * Ls]);
+  for (int k = 0; k < 12; ++k) v[k] = P::ld(get<NT>(p + k * Ls));
   if constexpr (P::NORM) {
-    const R n = f.norm[size_t(x) * Ls + s];
+    const R n = get<NT>(f.norm + size_t(x) * Ls + s);
 #pragma unroll
     for (int k = 0; k < 12; ++k) v[k] = n * v[k];
   }
@@ -160,7 +182,8 @@ __device__ __forceinline__ void load_half_spinor(CHalf<P> f, long x, int s, int 
   }
 }
 
-template <typename P>
+// NT: non-temporal, for fields a kernel streams beside gathers (see hop_body)
+template <typename P, bool NT = false>
 __device__ __forceinline__ void store_spinor(Half<P> f, long x, int s, int Ls, const cx<typename P::R> v[12]) {
   using R = typename P::R;
   typename P::S* p = f.data + size_t(x) * 12 * Ls + s;
@@ -170,12 +193,12 @@ __device__ __forceinline__ void store_spinor(Half<P> f, long x, int s, int Ls, c
     for (int k = 0; k < 12; ++k) m = fmaxf(m, fmaxf(fabsf(v[k].re), fabsf(v[k].im)));
     const R n = m > R(0) ? m : R(1);
     const R inv = R(1) / n;
-    f.norm[size_t(x) * Ls + s] = n;
+    put<NT>(f.norm + size_t(x) * Ls + s, n);
 #pragma unroll
-    for (int k = 0; k < 12; ++k) p[k * Ls] = P::st(inv * v[k]);
+    for (int k = 0; k < 12; ++k) put<NT>(p + k * Ls, P::st(inv * v[k]));
   } else {
 #pragma unroll
-    for (int k = 0; k < 12; ++k) p[k * Ls] = P::st(v[k]);
+    for (int k = 0; k < 12; ++k) put<NT>(p + k * Ls, P::st(v[k]));
   }
 }
 

@@ -588,13 +588,19 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
     } else {
       // (FP64 / FP32: the same pipelining was measured slower for the prologue and epilogue
       // variants, which already run at low occupancy)
+      // FP64 takes the two neighbours of one direction together: within a row of output sites
+      // they are the same sites, and the second read finds the first one's lines still cached (24^3
+      // x 64, Ls = 32: 2.08 -> 1.83 ms).  The smaller precisions take the forward directions first,
+      // which leaves more distinct lines in flight: in pairs the FP32 hops lose 4-6 % and the
+      // FP16 ones 12 %.
+      constexpr bool PAIRS = std::is_same<P, P64>::value;
       hop_dir<0, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
-      hop_dir<1, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
-      hop_dir<2, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
-      hop_dir<3, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
-      hop_dir<4, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
-      hop_dir<5, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
-      hop_dir<6, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
+      hop_dir<PAIRS ? 4 : 1, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
+      hop_dir<PAIRS ? 1 : 2, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
+      hop_dir<PAIRS ? 5 : 3, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
+      hop_dir<PAIRS ? 2 : 4, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
+      hop_dir<PAIRS ? 6 : 5, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
+      hop_dir<PAIRS ? 3 : 6, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
       hop_dir<7, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
     }
   }
@@ -665,6 +671,11 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
   // segment's shuffles read active lanes only)
   constexpr bool XS = CG && NS == 1 && RS == 0 && !ST && !std::is_same<P, P64>::value && (LS == 8 || LS == 16 || LS == 32);
   constexpr bool XSI = CG && RS > 0 && EPI < 2 && !std::is_same<P, P64>::value;  // per right-hand side
+  // In FP64 and FP32 the streamed operands (axpy operand, residual, outputs) are read and written
+  // non-temporally: they are not used again in this launch, and the L2 is left to the gathered
+  // spinors (24^3 x 64: FP64 Ls = 32 hops -4 to -10 %, FP32 Ls = 16 -2 to -4 %).  The 16-bit
+  // fields are better kept in the caches for the next kernel (fused CG hop +6 % with the hint).
+  constexpr bool NT = sizeof(typename P::S) >= 8;
   double nrm = 0.0;
   if constexpr (XS) __builtin_amdgcn_sched_barrier(0);  // (the operand's loads stay below the gathers: 128 -> 108 VGPRs)
   if (active) {
@@ -674,7 +685,7 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
       const int s = s0 + j * tps;
       if (a.x.data) {
         cx<R> xv[12];
-        load_spinor<P>(a.x, x, s, Ls, xv);
+        load_spinor<P, NT>(a.x, x, s, Ls, xv);
         if constexpr (XS) {
           if (a.x_es2) fifth_bidiagonal_apply<(LS > 0 ? LS : 1)>(xv, s, a.es2);
         } else if constexpr (XSI) {
@@ -686,10 +697,10 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
       if constexpr (CG) {
         // r -= alpha v: the CG residual update on the site this thread holds
         cx<R> rv[12];
-        load_spinor<P>(CHalf<P>{a.cg_r.data, a.cg_r.norm}, x, s, Ls, rv);
+        load_spinor<P, NT>(CHalf<P>{a.cg_r.data, a.cg_r.norm}, x, s, Ls, rv);
 #pragma unroll
         for (int k = 0; k < 12; ++k) rv[k] = {rv[k].re - alpha * acc[j][k].re, rv[k].im - alpha * acc[j][k].im};
-        store_spinor<P>(a.cg_r, x, s, Ls, rv);
+        store_spinor<P, NT>(a.cg_r, x, s, Ls, rv);
         if (a.norm_partials) {
 #pragma unroll
           for (int k = 0; k < 12; ++k)
@@ -702,7 +713,7 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
             nrm += double(acc[j][k].re) * double(acc[j][k].re) + double(acc[j][k].im) * double(acc[j][k].im);
         }
         // (no out with a second output: only the norm and out2 are wanted)
-        if (a.out.data) store_spinor<P>(a.out, x, s, Ls, acc[j]);
+        if (a.out.data) store_spinor<P, NT>(a.out, x, s, Ls, acc[j]);
       }
     }
   }
@@ -712,7 +723,7 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
     constexpr int SEG = RS > 0 ? RS : LS;
     if constexpr (RS > 0) fifth_scan_apply<SEG>(acc[0], sr, es_lds[EPI == 3 ? 1 : 0][rhs]);
     else fifth_scan_apply<SEG>(acc[0], s0, a.es2);
-    if (active) store_spinor<P>(a.out2, x, s0, Ls, acc[0]);
+    if (active) store_spinor<P, NT>(a.out2, x, s0, Ls, acc[0]);
   }
   if (a.norm_partials) {
     if constexpr (RS > 0) {
