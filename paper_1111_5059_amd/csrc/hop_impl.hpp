@@ -483,6 +483,35 @@ __device__ __forceinline__ void eo5_fifth_hop_f16(const HopArgs<P16>& a, float r
   }
 }
 
+// acc += ax X x at slice s (HopArgs::x_dir), one chirality at a time: the neighbouring slices'
+// halves come from the cache lines of the operand itself.
+// (The scheduling barriers keep these loads below the gathers and the second chirality's below the
+// first's arithmetic; without them FP64 went from 148 to 204 registers and FP16 spilled.)
+template <typename P>
+__device__ __forceinline__ void axpy_x_op(const HopArgs<P>& a, long x, int s, int Ls, cx<typename P::R> acc[12]) {
+  using R = typename P::R;
+#pragma unroll
+  for (int ch = 0; ch < 2; ++ch) {
+    __builtin_amdgcn_sched_barrier(0);
+    const int d = ch ? -a.x_dir : a.x_dir;
+    int sn = s + d;
+    const bool wrap = sn < 0 || sn >= Ls;
+    sn = sn < 0 ? Ls - 1 : sn >= Ls ? 0 : sn;
+    R xa = a.xa, xb = a.xb;
+    if (a.pbs) {
+      xa = a.pbs[s] * a.xdd + R(1);
+      xb = a.pcs[a.x_dir < 0 ? s : sn] * a.xdd - R(1);
+    }
+    if (wrap) xb = -a.pm * xb;
+    cx<R> xv[6], nv[6];
+    load_half_spinor<P>(a.x, x, s, Ls, ch * 6, xv);
+    load_half_spinor<P>(a.x, x, sn, Ls, ch * 6, nv);
+#pragma unroll
+    for (int k = 0; k < 6; ++k) acc[ch * 6 + k] = acc[ch * 6 + k] + a.ax * (xa * xv[k] + xb * nv[k]);
+  }
+  __builtin_amdgcn_sched_barrier(0);
+}
+
 template <typename P, int LS, int NS, bool DAG, bool PRO, int EPI, bool LL, bool CG, bool ST, int RS = 0,
           bool EO5 = false>
 __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pidx, int spb) {
@@ -670,6 +699,8 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
   // the site's segment right after the read (every lane of a site is active or inactive together, so the
   // segment's shuffles read active lanes only)
   constexpr bool XS = CG && NS == 1 && RS == 0 && !ST && !std::is_same<P, P64>::value && (LS == 8 || LS == 16 || LS == 32);
+  // the axpy operand through X = xa + xb S, its neighbouring slices read beside it (x_dir)
+  constexpr bool XOP = x_op_prec<P>() && !CG && EPI == 0 && RS == 0 && !ST && !EO5;
   constexpr bool XSI = CG && RS > 0 && EPI < 2 && !std::is_same<P, P64>::value;  // per right-hand side
   // In FP64 and FP32 the streamed operands (axpy operand, residual, outputs) are read and written
   // non-temporally: they are not used again in this launch, and the L2 is left to the gathered
@@ -683,7 +714,14 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
 #pragma unroll
     for (int j = 0; j < NS; ++j) {
       const int s = s0 + j * tps;
-      if (a.x.data) {
+      bool x_done = false;
+      if constexpr (XOP) {
+        if (a.x_dir) {
+          axpy_x_op<P>(a, x, s, Ls, acc[j]);
+          x_done = true;
+        }
+      }
+      if (a.x.data && !x_done) {
         cx<R> xv[12];
         load_spinor<P, NT>(a.x, x, s, Ls, xv);
         if constexpr (XS) {
@@ -971,6 +1009,7 @@ int launch_hop(const HopArgs<P>& a, bool dagger, bool prologue, const LaunchCfg&
   // lane, the site's Ls lanes a wave segment)
   const bool seg_shape = cfg.ns == 1 && (a.Ls == 8 || a.Ls == 16 || a.Ls == 32);
   if (a.x_es2 && (!a.cg_r.data || !a.x.data || !x_es2_shape<P>(cfg, a.Ls) || batch)) return -1;
+  if (a.x_dir && (!x_op_prec<P>() || !a.x.data || a.cg_r.data || a.E || a.epi_scan || stage_shape(cfg, a.Ls) || batch)) return -1;
   if (a.x_es2 && (a.es2.ch[0].has_inv || a.es2.ch[1].has_inv)) return -1;  // (bidiagonal operators only)
   if (!a.cg_r.data && !a.out.data && !(a.out2.data && a.E && a.epi_scan && seg_shape)) return -1;
   const int threads = cfg.spb * (a.Ls / cfg.ns);

@@ -43,6 +43,13 @@ struct HopArgs {
   int epi_scan = 0;            // es is valid (used when the site's lanes form a wave segment)
   CHalf<P> x;                  // axpy operand (data == nullptr: none)
   typename P::R ax;
+  // x_dir != 0 (launches without epilogue or fused CG step): the axpy operand is X . x with the
+  // bidiagonal site-local operator X = xa + xb S, S taking slice s + x_dir in chirality 0 and
+  // s - x_dir in chirality 1 (-pm across the boundary); with s-dependent coefficients (pbs, pcs
+  // given) xa = b_s xdd + 1 and xb = c_s' xdd - 1, s' the row of the untransposed operator (x_dir -1:
+  // s; +1, the adjoint: the slice read)
+  int x_dir = 0;
+  typename P::R xa = 0, xb = 0, xdd = 0;
   // x_es2 != 0 (fused CG step, scan epilogue shapes only): the axpy operand is es2 . x, the
   // bidiagonal site-local operator applied to x in registers (the CG hop then reads A^-dag q, which it
   // turns back into q = A^dag (A^-dag q), and q itself need not be stored); interleaved right-
@@ -72,6 +79,11 @@ struct HopArgs {
   int sigma = 0;
   typename P::R r5 = 0;
 };
+
+// the precisions whose launches take an operator on the axpy operand (HopArgs::x_dir): not FP16, whose
+// hops would spill at the five waves per SIMD they run with
+template <typename P>
+constexpr bool x_op_prec() { return !std::is_same<P, P16>::value; }
 
 struct LaunchCfg {
   int spb;        // 4D sites per block

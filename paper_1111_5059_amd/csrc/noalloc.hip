@@ -133,7 +133,7 @@ static int noalloc_t(dwf_ctx* ctx, const dwf_params& p, const void* U, const voi
   }
   const S* links = reinterpret_cast<const S*>(U);
   auto hop = [&](int out_par, CHalf<P> src, Half<P> dst, bool dag, bool pro, double scale, int slot,
-                 CHalf<P> x = {nullptr, nullptr}, double ax = 0.0) {
+                 CHalf<P> x = {nullptr, nullptr}, double ax = 0.0, bool x_a = false) {
     HopArgs<P> a;
     a.in = src;
     a.out = dst;
@@ -153,6 +153,12 @@ static int noalloc_t(dwf_ctx* ctx, const dwf_params& p, const void* U, const voi
     }
     a.x = x;
     a.ax = R(ax);
+    if (x_a) {  // the axpy operand through A (A^dag), as Op::hop_a
+      const double d = 4.0 - p.M5;
+      a.x_dir = dag ? +1 : -1;
+      a.xa = R(p.b * d + 1.0);
+      a.xb = R(p.c * d - 1.0);
+    }
     a.norm_partials = nullptr;
     DWF_CHECK_LAUNCH(launch_hop<P>(a, dag, pro && moebius, cfg, st));
   };
@@ -186,15 +192,16 @@ static int noalloc_t(dwf_ctx* ctx, const dwf_params& p, const void* U, const voi
       char* ob = reinterpret_cast<char*>(out);
       const CHalf<P> ie = chalf_view<P>(ib, ns, Ls), io = chalf_view<P>(ib + hb, ns, Ls);
       const Half<P> oe = half_view<P>(ob, ns, Ls), oo = half_view<P>(ob + hb, ns, Ls);
+      // (the Shamir operator: no input factor, no F^dag; A as in Op::full)
+      if (x_op_prec<P>()) {
+        hop(0, io, oe, dagger != 0, false, -0.5, -1, ie, 1.0, true);
+        hop(1, ie, oo, dagger != 0, false, -0.5, -1, io, 1.0, true);
+        return DWF_OK;
+      }
       fifth(ie, oe, dagger ? E_ADAG : E_A);
       fifth(io, oo, dagger ? E_ADAG : E_A);
-      if (!dagger) {
-        hop(0, io, oe, false, true, -0.5, -1, CHalf<P>{oe.data, oe.norm}, 1.0);
-        hop(1, ie, oo, false, true, -0.5, -1, CHalf<P>{oo.data, oo.norm}, 1.0);
-      } else {
-        hop(0, io, oe, true, false, -0.5, moebius ? E_FDAG : -1, CHalf<P>{oe.data, oe.norm}, 1.0);
-        hop(1, ie, oo, true, false, -0.5, moebius ? E_FDAG : -1, CHalf<P>{oo.data, oo.norm}, 1.0);
-      }
+      hop(0, io, oe, dagger != 0, false, -0.5, -1, CHalf<P>{oe.data, oe.norm}, 1.0);
+      hop(1, ie, oo, dagger != 0, false, -0.5, -1, CHalf<P>{oo.data, oo.norm}, 1.0);
       return DWF_OK;
     }
     case DWF_OP_A:

@@ -267,6 +267,29 @@ struct Op {
     DWF_CHECK_LAUNCH(launch_hop<P>(a, dag, pro && moebius, cfg, ctx->stream));
     if (mark >= 0) timer_end(ctx, mark, hop_bytes(a));
   }
+  // ... with the axpy operand A x (dag: A^dag x): out = A x + scale H [F] in
+  void hop_a(int out_par, CHalf<P> in, Half<P> out, bool dag, bool pro, double scale, CHalf<P> x) const {
+    HopArgs<P> a = hop_args(out_par, in, out, nullptr, scale, x, 1.0);
+    const double d = 4.0 - M5;
+    a.x_dir = dag ? +1 : -1;
+    a.xa = R(b * d + 1.0);
+    a.xb = R(c * d - 1.0);
+    a.xdd = R(d);
+    long mark = -1;
+    if (ctx->timer.on) mark = timer_begin(ctx, hop_name(a, dag, pro && moebius, cfg));
+    DWF_CHECK_LAUNCH(launch_hop<P>(a, dag, pro && moebius, cfg, ctx->stream));
+    if (mark >= 0) timer_end(ctx, mark, hop_bytes(a));
+  }
+  // F in for a hop that then runs without the input factor: in tmp where the storage precision is
+  // that of the arithmetic (FP64, FP32), else not at all (the 16-bit formats keep F in registers,
+  // in the hop's prologue, so that it is not rounded).  The prologue triples the neighbour loads of
+  // a hop that its gathers bound; F as a pass of its own is two streamed fields (FP64, Ls = 16, 24^3 x
+  // 64: prologue hop 2.1 ms, plain hop and pass 1.5 ms).  Returns whether tmp holds F in.
+  bool input_factor(CHalf<P> in, Half<P> tmp) const {
+    if (!moebius || !tmp.data || sizeof(S) < 8) return false;
+    fifth(in, tmp, E_F);
+    return true;
+  }
   // the template instance launch_hop selects for these arguments and launch shape (kernel name as
   // demangled; batch: the batched kernel)
   std::string hop_name(const HopArgs<P>& a, bool dag, bool pro, const LaunchCfg& cfg, bool batch = false) const {
@@ -298,13 +321,15 @@ struct Op {
   bool rebuild_q_ok() const { return second_output_ok() && x_es2_shape<P>(cfg, Ls); }
   // workgroups of one hop launch (the norm partials it writes)
   long hop_blocks() const { return (g->nsites + cfg.spb - 1) / cfg.spb; }
-  // M_prec psi = psi - 1/4 A^-1 H_oe F A^-1 H_eo F psi      (odd -> odd);
+  // M_prec psi = psi - 1/4 A^-1 H_oe (F A^-1) H_eo F psi    (odd -> odd); tmp_f (optional, Moebius):
+  // room for F psi (see input_factor);
   // ainvdag_out (optional, see second_output_ok): also A^-dag (M_prec psi); with it, out may be
   // empty (the norm partials and A^-dag (M_prec psi) only)
   void mprec(CHalf<P> in, Half<P> out, Half<P> tmp_e, double* partials = nullptr,
-             Half<P> ainvdag_out = {nullptr, nullptr}) const {
-    hop(0, in, tmp_e, false, true, 1.0, em(E_AINV));
-    hop(1, cv(tmp_e), out, false, true, -0.25, em(E_AINV), in, 1.0, partials, CgStep(), ainvdag_out, E_AINVDAG);
+             Half<P> ainvdag_out = {nullptr, nullptr}, Half<P> tmp_f = {nullptr, nullptr}) const {
+    const bool f = input_factor(in, tmp_f);
+    hop(0, f ? cv(tmp_f) : in, tmp_e, false, !f, 1.0, em(moebius ? E_F_AINV : E_AINV));
+    hop(1, cv(tmp_e), out, false, false, -0.25, em(E_AINV), in, 1.0, partials, CgStep(), ainvdag_out, E_AINVDAG);
   }
   // M_prec psi from fpsi = F psi prepared by the caller (the CG p update): both hops without
   // the input factor, the first with the epilogue F A^-1 (Moebius operators)
@@ -336,16 +361,29 @@ struct Op {
         reb ? cv(tmp_o) : in, 1.0, partials, cg);
   }
   // full D (or D^dag):  (D psi)_p = A psi_p - 1/2 H F psi_{1-p};  (D^dag psi)_p = A^dag psi_p - 1/2 F^dag H^dag psi_{1-p}
-  void full(CHalf<P> in_e, CHalf<P> in_o, Half<P> out_e, Half<P> out_o, bool dag) const {
-    fifth(in_e, out_e, dag ? E_ADAG : E_A);
-    fifth(in_o, out_o, dag ? E_ADAG : E_A);
-    if (!dag) {
-      hop(0, in_o, out_e, false, true, -0.5, nullptr, cv(out_e), 1.0);
-      hop(1, in_e, out_o, false, true, -0.5, nullptr, cv(out_o), 1.0);
-    } else {
-      hop(0, in_o, out_e, true, false, -0.5, moebius ? em(E_FDAG) : nullptr, cv(out_e), 1.0);
-      hop(1, in_e, out_o, true, false, -0.5, moebius ? em(E_FDAG) : nullptr, cv(out_o), 1.0);
+  // A is applied to the hop's axpy operand as it is read (a pass of its own reads and writes every
+  // field once more: 6.17 -> 4.33 ms in FP64 at 24^3 x 64, Ls = 32), except beside the epilogue of the
+  // Moebius adjoint and in FP16; tmp_f (optional, Moebius): room for F psi_{1-p}
+  void full(CHalf<P> in_e, CHalf<P> in_o, Half<P> out_e, Half<P> out_o, bool dag,
+            Half<P> tmp_f = {nullptr, nullptr}) const {
+    if (dag && moebius) {
+      fifth(in_e, out_e, E_ADAG);
+      fifth(in_o, out_o, E_ADAG);
+      hop(0, in_o, out_e, true, false, -0.5, em(E_FDAG), cv(out_e), 1.0);
+      hop(1, in_e, out_o, true, false, -0.5, em(E_FDAG), cv(out_o), 1.0);
+      return;
     }
+    if (!x_op_prec<P>()) {
+      fifth(in_e, out_e, dag ? E_ADAG : E_A);
+      fifth(in_o, out_o, dag ? E_ADAG : E_A);
+      hop(0, in_o, out_e, dag, !dag, -0.5, nullptr, cv(out_e), 1.0);
+      hop(1, in_e, out_o, dag, !dag, -0.5, nullptr, cv(out_o), 1.0);
+      return;
+    }
+    bool f = input_factor(in_o, tmp_f);
+    hop_a(0, f ? cv(tmp_f) : in_o, out_e, dag, !f && !dag, -0.5, in_e);
+    f = input_factor(in_e, tmp_f);
+    hop_a(1, f ? cv(tmp_f) : in_e, out_o, dag, !f && !dag, -0.5, in_o);
   }
 };
 
@@ -454,8 +492,9 @@ struct Op5 {
   }
   // S psi = d0 psi - K_eo K_oe psi / d0  (even -> even; tmp: an odd field)
   void mprec(CHalf<P> in, Half<P> out, Half<P> tmp, double* partials = nullptr,
-             Half<P> unused = {nullptr, nullptr}) const {
+             Half<P> unused = {nullptr, nullptr}, Half<P> unused_f = {nullptr, nullptr}) const {
     (void)unused;
+    (void)unused_f;
     K(1, in, tmp, false, 0.5, 1.0);
     K(0, cv(tmp), out, false, -0.5 / d0, -1.0 / d0, in, d0, partials);
   }

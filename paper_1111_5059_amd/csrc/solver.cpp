@@ -79,7 +79,7 @@ static int cg_normal(dwf_ctx* ctx, const OpT<P64>& op64, const OpT<Pi>& opi, CHa
   Half<P64> t64b = hview<P64>(ws_get(ctx, tag + ".t64b", hb64), g, Ls);
   Half<P64> t64c = hview<P64>(ws_get(ctx, tag + ".t64c", hb64), g, Ls);
   auto true_residual = [&]() -> double {
-    op64.mprec(cv(x), t64a, t64b);
+    op64.mprec(cv(x), t64a, t64b, nullptr, Half<P64>{nullptr, nullptr}, t64c);
     op64.mprec_dag(cv(t64a), rhi, t64b, t64c);
     DWF_CHECK_LAUNCH(launch_axpby<P64>(1.0, rhs, -1.0, rhi, n5, Ls, s));
     return norm2_sync<P64>(ctx, cv(rhi), g, Ls);
@@ -401,7 +401,8 @@ int solve_full(dwf_ctx* ctx, const dwf_params& p, const void* U64, const void* b
   } else {
     // source preparation
     op.fifth(be, te, E_AINV);                                  // A^-1 b_e
-    op.hop(1, cv(te), to, false, true, 0.5, nullptr, bo, 1.0);  // b_o - B_oe A^-1 b_e
+    const bool f = op.input_factor(cv(te), bp);
+    op.hop(1, f ? cv(bp) : cv(te), to, false, !f, 0.5, nullptr, bo, 1.0);  // b_o - B_oe A^-1 b_e
     op.fifth(cv(to), bp, E_AINV);                              // b'_o
     op.mprec_dag(cv(bp), rhs, te, t2);                         // M^dag b'
     double tol_n = tol;
@@ -411,10 +412,11 @@ int solve_full(dwf_ctx* ctx, const dwf_params& p, const void* U64, const void* b
       if (left <= 0) break;
       normal_solve(ctx, p, U64, cv(rhs), xo, tol_n, left, delta, tag + ".cg", &st);
       // x_e = A^-1 (b_e - B_eo x_o)
-      op.hop(0, cv(xo), te, false, true, 0.5, nullptr, be, 1.0);
+      const bool f = op.input_factor(cv(xo), t2);
+      op.hop(0, f ? cv(t2) : cv(xo), te, false, !f, 0.5, nullptr, be, 1.0);
       op.fifth(cv(te), xe, E_AINV);
       // true residual of the full system
-      op.full(cv(xe), cv(xo), re, ro, false);
+      op.full(cv(xe), cv(xo), re, ro, false, t2);
       DWF_CHECK_LAUNCH(launch_axpby<P64>(1.0, be, -1.0, re, n5, Ls, s));
       DWF_CHECK_LAUNCH(launch_axpby<P64>(1.0, bo, -1.0, ro, n5, Ls, s));
       const double r2 = norm2_sync<P64>(ctx, cv(re), g, Ls) + norm2_sync<P64>(ctx, cv(ro), g, Ls);
@@ -539,7 +541,7 @@ static void cg_batched_ilv(dwf_ctx* ctx, std::vector<BatchSys*> sys, double delt
   auto true_residual = [&](BatchSys& b) -> double {
     Half<P64> rhi = hview<P64>(rhi_raw, g, RS), ta = hview<P64>(t64a_raw, g, RS), tb = hview<P64>(t64b_raw, g, RS),
               tc = hview<P64>(t64c_raw, g, RS);
-    b.op64->mprec(cv(b.x), ta, tb);
+    b.op64->mprec(cv(b.x), ta, tb, nullptr, Half<P64>{nullptr, nullptr}, tc);
     b.op64->mprec_dag(cv(ta), rhi, tb, tc);
     DWF_CHECK_LAUNCH(launch_axpby<P64>(1.0, b.rhs, -1.0, rhi, ns * RS, RS, s));
     return norm2_sync<P64>(ctx, cv(rhi), g, RS);
@@ -855,7 +857,7 @@ static void cg_batched_fields(dwf_ctx* ctx, std::vector<BatchSys>& S, int maxit,
     const int Ls = b.p.Ls;
     Half<P64> rhi = hview<P64>(rhi_raw, b.g, Ls), ta = hview<P64>(t64a_raw, b.g, Ls), tb = hview<P64>(t64b_raw, b.g, Ls),
               tc = hview<P64>(t64c_raw, b.g, Ls);
-    b.op64->mprec(cv(b.x), ta, tb);
+    b.op64->mprec(cv(b.x), ta, tb, nullptr, Half<P64>{nullptr, nullptr}, tc);
     b.op64->mprec_dag(cv(ta), rhi, tb, tc);
     DWF_CHECK_LAUNCH(launch_axpby<P64>(1.0, b.rhs, -1.0, rhi, b.g->nsites * Ls, Ls, s));
     return norm2_sync<P64>(ctx, cv(rhi), b.g, Ls);
@@ -1134,7 +1136,8 @@ int solve_batched(dwf_ctx* ctx, int nrhs, const dwf_params* P, const void* const
     b2[k] = norm2_sync<P64>(ctx, be, B.g, Ls) + norm2_sync<P64>(ctx, bo, B.g, Ls);
     if (!std::isfinite(b2[k])) throw Error{DWF_ERR_NAN, "non-finite source"};
     B.op64->fifth(be, te, E_AINV);
-    B.op64->hop(1, cv(te), to, false, true, 0.5, nullptr, bo, 1.0);
+    const bool f = B.op64->input_factor(cv(te), bp);
+    B.op64->hop(1, f ? cv(bp) : cv(te), to, false, !f, 0.5, nullptr, bo, 1.0);
     B.op64->fifth(cv(to), bp, E_AINV);
     B.op64->mprec_dag(cv(bp), rhs, te, t2);
     (void)n5;
@@ -1190,9 +1193,11 @@ int solve_batched(dwf_ctx* ctx, int nrhs, const dwf_params* P, const void* const
       Half<P64> te = hview<P64>(ws_get(ctx, "batchfull.se", hb), B.g, Ls);
       void* rf = ws_get(ctx, "batchfull.rfull", 2 * hb);
       Half<P64> re = hview<P64>(rf, B.g, Ls), ro = hview<P64>(reinterpret_cast<char*>(rf) + hb, B.g, Ls);
-      B.op64->hop(0, cv(B.x), te, false, true, 0.5, nullptr, be, 1.0);
+      Half<P64> t2 = hview<P64>(ws_get(ctx, "batchfull.t2", hb), B.g, Ls);
+      const bool f = B.op64->input_factor(cv(B.x), t2);
+      B.op64->hop(0, f ? cv(t2) : cv(B.x), te, false, !f, 0.5, nullptr, be, 1.0);
       B.op64->fifth(cv(te), xe, E_AINV);
-      B.op64->full(cv(xe), cv(B.x), re, ro, false);
+      B.op64->full(cv(xe), cv(B.x), re, ro, false, t2);
       DWF_CHECK_LAUNCH(launch_axpby<P64>(1.0, be, -1.0, re, n5, Ls, s));
       DWF_CHECK_LAUNCH(launch_axpby<P64>(1.0, bo, -1.0, ro, n5, Ls, s));
       const double r2 = norm2_sync<P64>(ctx, cv(re), B.g, Ls) + norm2_sync<P64>(ctx, cv(ro), B.g, Ls);
@@ -1290,7 +1295,8 @@ int madwf(dwf_ctx* ctx, const dwf_params& pt, const dwf_params& pi, const void* 
     for (int par = 0; par < 2; ++par)
       DWF_CHECK_LAUNCH(launch_slice_copy(CH(c, par, L, hb), L, 0, H(cp, par, Lp, hbp), Lp, 0, 1.0, ns, s));
     pshift(cp, zp, 0, Lp, hbp);
-    opi1.full(CH(zp, 0, Lp, hbp), CH(zp, 1, Lp, hbp), H(rp, 0, Lp, hbp), H(rp, 1, Lp, hbp), false);
+    opi1.full(CH(zp, 0, Lp, hbp), CH(zp, 1, Lp, hbp), H(rp, 0, Lp, hbp), H(rp, 1, Lp, hbp), false,
+              H(yp, 0, Lp, hbp));
     // D'(m) z = rhs'
     DWF_CHECK_LAUNCH(launch_zero(zp, 2 * hbp, s));
     std::memset(&si, 0, sizeof(si));
@@ -1350,13 +1356,16 @@ static void force_terms(dwf_ctx* ctx, const Op<P64>& op, const void* Unat, CHalf
   Half<P64> Ze = hview<P64>(ws_get(ctx, "force.Ze", hb), g, Ls);
   Half<P64> We = hview<P64>(ws_get(ctx, "force.We", hb), g, Ls);
   Half<P64> Wo = hview<P64>(ws_get(ctx, "force.Wo", hb), g, Ls);
-  op.hop(0, X, Xe, false, true, -0.5, op.em(E_AINV));                   // X_e = A^-1 B_eo X
+  // W_o = F X, X_e = A^-1 B_eo X = -1/2 A^-1 H W_o, W_e = F X_e (Shamir: F = 1)
+  if (op.moebius) op.fifth(X, Wo, E_F);
+  const CHalf<P64> wo = op.moebius ? cv(Wo) : X;
+  op.hop(0, wo, Xe, false, false, -0.5, op.em(E_AINV));
+  if (op.moebius) op.fifth(cv(Xe), We, E_F);
+  const CHalf<P64> we = op.moebius ? cv(We) : cv(Xe);
   op.fifth(Y, Zo, E_AINVDAG);                                           // Y_o' = A^-dag Y
   op.hop(0, cv(Zo), Ze, true, false, -0.5, op.em(E_AINVDAG_FDAG));      // Y_e' = A^-dag B_oe^dag Y_o'
-  op.fifth(X, Wo, E_F);                                                 // W_o = F X
-  op.fifth(cv(Xe), We, E_F);                                            // W_e = F X_e
   const long mark = ctx->timer.on ? timer_begin(ctx, "force_kernel") : -1;
-  DWF_CHECK_LAUNCH(launch_force(g->tables(), Ls, cv(We), cv(Wo), cv(Ze), cv(Zo),
+  DWF_CHECK_LAUNCH(launch_force(g->tables(), Ls, we, wo, cv(Ze), cv(Zo),
                                 reinterpret_cast<const double2*>(Unat), g->tbc, g->dims, kind,
                                 reinterpret_cast<double2*>(Fout), ctx->stream, coef, accumulate));
   // algorithmic bytes: the four FP64 half fields W_e, W_o, Z_e, Z_o and the links read once, the

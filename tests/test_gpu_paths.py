@@ -36,3 +36,43 @@ def test_cyclic_recurrence(env, ora, Ls, prec, mass, M5):
         ref = mask(ora.fifth(po, psi, "Ainv" + ("dag" if dag else "")), dims, 0)
         err = rel_err(lat.unpack_np(dst, dwf.KIND_EVEN, P), ref)
         assert err < PREC_TOL[prec], (dag, err)
+
+
+@pytest.mark.parametrize("Ls", [2, 7, 16])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("kind", ["shamir", "moebius", "sdep"])
+def test_full_operator_and_input_factor(env, ora, Ls, prec, kind):
+    """D and D^dag with A applied to the hop's axpy operand (both chiralities' boundaries, odd and
+    smallest extents, coefficients per slice), and H F and M_prec with the input factor in a pass of
+    its own (FP64, FP32) or in the hop (16-bit)."""
+    dwf, ctx = env
+    P = dwf.PREC_NAMES[prec]
+    dims = (4, 2, 6, 2)
+    kw, okw = {}, {}
+    if kind == "moebius":
+        kw = okw = {"b": 1.5, "c": 0.5}
+    elif kind == "sdep":
+        w = 1.5 + 0.5 * np.sin(np.arange(Ls))
+        kw = {"b_s": (w + 1) / 2, "c_s": (w - 1) / 2}
+        okw = {"bs": kw["b_s"], "cs": kw["c_s"]}
+    U = synth.random_links(dims, 0.5, 870)
+    psi = synth.gaussian_spinor(dims, Ls, 871 + Ls)
+    lat = dwf.Lattice(ctx, dims, Ls, mass=0.2, tbc=1, **kw)
+    po = ora.params(dims, Ls, mass=0.2, tbc=1, **okw)
+    Ug, p = lat.pack_gauge(U, P), lat.params(P)
+    src = lat.pack(psi, dwf.KIND_FULL, P)
+    for dag in (False, True):
+        dst = lat.empty(dwf.KIND_FULL, P)
+        dwf.mobius_dslash(ctx, p, Ug, src, dst, dwf.OP_FULL, 0, dag)
+        err = rel_err(lat.unpack_np(dst, dwf.KIND_FULL, P), ora.dwf(po, U, psi, dagger=dag))
+        assert err < PREC_TOL[prec], ("D", dag, err)
+    psio = mask(psi, dims, 1)
+    srco = lat.pack(psio, dwf.KIND_ODD, P)
+    out = lat.empty(dwf.KIND_ODD, P)
+    dwf.mobius_dslash(ctx, p, Ug, srco, out, dwf.OP_MPREC, 1, False)
+    err = rel_err(lat.unpack_np(out, dwf.KIND_ODD, P), ora.mprec(po, U, psio))
+    assert err < PREC_TOL[prec], ("M", err)
+    dwf.mobius_dslash(ctx, p, Ug, srco, out, dwf.OP_HOP, 0, False)
+    ref = ora.hop5(po, U, ora.fifth(po, psio, "F"), out_parity=0)
+    err = rel_err(lat.unpack_np(out, dwf.KIND_EVEN, P), ref)
+    assert err < PREC_TOL[prec], ("HF", err)
