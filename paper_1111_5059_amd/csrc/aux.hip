@@ -355,30 +355,63 @@ int launch_slice_copy(CHalf<P64> in, int Ls_in, int s_in, Half<P64> out, int Ls_
 }
 
 // 4D even-odd field halves <-> 5D-parity fields.  Slice s of 4D parity q belongs to the 5D
-// parity (s + q) mod 2, where it is slot s / 2 of half q: element ((q nsites + x) 12 + k) Ls/2 + s/2
-// (FP16 norm: (q nsites + x) Ls/2 + s/2).  Thread per element of the 4D fields (grid-stride).
-template <typename P>
-__global__ void __launch_bounds__(256) eo5_split_kernel(Half<P> h0, Half<P> h1, Half<P> f5e, Half<P> f5o, long nsites,
-                                                        int Ls, int merge) {
-  const long per = nsites * 12 * Ls;
-  const int LH = Ls / 2;
-  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < 2 * per; i += (long)gridDim.x * blockDim.x) {
-    const int q = i >= per ? 1 : 0;
-    const long r = i - q * per;
-    const long xk = r / Ls;  // x_cb * 12 + k
-    const int s = int(r - xk * Ls);
-    const Half<P> h = q ? h1 : h0;
-    const Half<P> f5 = ((s + q) & 1) ? f5o : f5e;
-    const long j5 = (q * nsites * 12 + xk) * LH + (s >> 1);
-    if (merge) h.data[r] = f5.data[j5];
-    else f5.data[j5] = h.data[r];
+// parity (s + q) mod 2, where it is slot s / 2 of half q.  Slices 2j and 2j + 1 of a row are adjacent
+// in the 4D half and have the same index in the two 5D fields, so pair i of half q (i = (x 12 + k)
+// Ls/2 + j) goes to element q npair + i of both, with no index arithmetic; the FP16 norms are pairs in
+// the same way.  VP pairs per thread: 16-byte accesses for the 4- and 8-byte storage types.  A
+// parity that is not wanted (data == nullptr) is not written by a split and is zero in a merge.
+// (Bound by HBM: at 16^3 x 32, Ls = 16 in FP16 a split of both parities took 90 us with one element
+// and two 64-bit divisions per thread.)
+template <typename T, int VP>
+struct alignas(sizeof(T) * VP * 2) PairVec {
+  T v[2 * VP];
+};
+template <typename T, int VP>
+struct alignas(sizeof(T) * VP) SlotVec {
+  T v[VP];
+};
+
+template <typename T, int VP>
+__device__ __forceinline__ void split_pairs(T* full, T* f0, T* f1, long i, int merge) {
+  // full: element pairs; f0, f1: the slots of the pairs' first and second elements
+  PairVec<T, VP> p;
+  SlotVec<T, VP> a, b;
+  if (merge) {
+    for (int k = 0; k < VP; ++k) a.v[k] = b.v[k] = T{};
+    if (f0) a = reinterpret_cast<const SlotVec<T, VP>*>(f0)[i];
+    if (f1) b = reinterpret_cast<const SlotVec<T, VP>*>(f1)[i];
+#pragma unroll
+    for (int k = 0; k < VP; ++k) {
+      p.v[2 * k] = a.v[k];
+      p.v[2 * k + 1] = b.v[k];
+    }
+    reinterpret_cast<PairVec<T, VP>*>(full)[i] = p;
+  } else {
+    p = reinterpret_cast<const PairVec<T, VP>*>(full)[i];
+#pragma unroll
+    for (int k = 0; k < VP; ++k) {
+      a.v[k] = p.v[2 * k];
+      b.v[k] = p.v[2 * k + 1];
+    }
+    if (f0) reinterpret_cast<SlotVec<T, VP>*>(f0)[i] = a;
+    if (f1) reinterpret_cast<SlotVec<T, VP>*>(f1)[i] = b;
+  }
+}
+
+template <typename P, int VP>
+__global__ void __launch_bounds__(256) eo5_split_kernel(Half<P> h0, Half<P> h1, Half<P> f5e, Half<P> f5o, long npair,
+                                                        long nnorm, int merge) {
+  using S = typename P::S;
+  const int q = blockIdx.y;
+  const Half<P> h = q ? h1 : h0;
+  // even slices of 4D parity q belong to the 5D parity q
+  const Half<P> a = q ? f5o : f5e, b = q ? f5e : f5o;
+  for (long i = (long)blockIdx.x * blockDim.x + threadIdx.x; i < npair / VP; i += (long)gridDim.x * blockDim.x) {
+    split_pairs<S, VP>(h.data, a.data ? a.data + q * npair : nullptr, b.data ? b.data + q * npair : nullptr, i, merge);
     if constexpr (P::NORM) {
-      const long x = xk / 12;
-      if (xk - x * 12 == 0) {
-        const long n4 = x * Ls + s, n5 = (q * nsites + x) * LH + (s >> 1);
-        if (merge) h.norm[n4] = f5.norm[n5];
-        else f5.norm[n5] = h.norm[n4];
-      }
+      if (i < nnorm)
+        split_pairs<float, 1>(h.norm, a.norm ? a.norm + q * nnorm : nullptr, b.norm ? b.norm + q * nnorm : nullptr, i,
+                              merge);
     }
   }
 }
@@ -387,11 +420,22 @@ template <typename P>
 int launch_eo5_split(Half<P> h0, Half<P> h1, Half<P> f5_even, Half<P> f5_odd, long nsites, int Ls, int merge,
                      hipStream_t st) {
   if (Ls < 2 || Ls % 2 || nsites <= 0) return -1;
-  const long n = 2 * nsites * 12 * Ls;
+  const long npair = nsites * 12 * (Ls / 2), nnorm = nsites * (Ls / 2);
+  // two pairs per thread need an even number of them and fields aligned to the vectors
+  auto aligned = [](const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; };
+  const bool wide = sizeof(typename P::S) <= 8 && npair % 2 == 0 && aligned(h0.data) && aligned(h1.data) &&
+                    aligned(f5_even.data) && aligned(f5_odd.data) && sizeof(typename P::S) * 2 <= 16;
+  const long n = wide ? npair / 2 : npair;  // (at least nnorm either way)
   long blocks = (n + 255) / 256;
   if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL((eo5_split_kernel<P>), dim3((unsigned)blocks), dim3(256), 0, st, h0, h1, f5_even, f5_odd, nsites,
-                     Ls, merge);
+  const dim3 grid((unsigned)blocks, 2);
+  if constexpr (sizeof(typename P::S) <= 8) {
+    if (wide) {
+      hipLaunchKernelGGL((eo5_split_kernel<P, 2>), grid, dim3(256), 0, st, h0, h1, f5_even, f5_odd, npair, nnorm, merge);
+      return hipGetLastError() == hipSuccess ? 0 : -2;
+    }
+  }
+  hipLaunchKernelGGL((eo5_split_kernel<P, 1>), grid, dim3(256), 0, st, h0, h1, f5_even, f5_odd, npair, nnorm, merge);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 template int launch_eo5_split<P64>(Half<P64>, Half<P64>, Half<P64>, Half<P64>, long, int, int, hipStream_t);

@@ -125,7 +125,8 @@ template <typename P>
 int launch_hop_eo5(const HopArgs<P>& a0, const HopArgs<P>& a1, bool dagger, const LaunchCfg& cfg, hipStream_t st);
 // The two 4D-parity halves h0, h1 of a field ([x_cb][12][Ls] each) <-> its two 5D-parity fields
 // ([4D parity q][x_cb][12][Ls/2] each: slice s of 4D parity q lies in field (s + q) mod 2, slot
-// s / 2); merge = 0 splits, 1 merges
+// s / 2); merge = 0 splits, 1 merges.  A 5D field without data is not wanted by a split and zero in
+// a merge.
 template <typename P>
 int launch_eo5_split(Half<P> h0, Half<P> h1, Half<P> f5_even, Half<P> f5_odd, long nsites, int Ls, int merge,
                      hipStream_t st);

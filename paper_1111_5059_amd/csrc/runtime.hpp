@@ -269,12 +269,17 @@ struct Op {
   }
   // ... with the axpy operand A x (dag: A^dag x): out = A x + scale H [F] in
   void hop_a(int out_par, CHalf<P> in, Half<P> out, bool dag, bool pro, double scale, CHalf<P> x) const {
-    HopArgs<P> a = hop_args(out_par, in, out, nullptr, scale, x, 1.0);
     const double d = 4.0 - M5;
+    hop_x(out_par, in, out, dag, pro, scale, x, b * d + 1.0, c * d - 1.0);
+  }
+  // ... with the axpy operand (xa + xb S~) x (dag: its adjoint; s-dependent coefficients: always A)
+  void hop_x(int out_par, CHalf<P> in, Half<P> out, bool dag, bool pro, double scale, CHalf<P> x, double xa,
+             double xb) const {
+    HopArgs<P> a = hop_args(out_par, in, out, nullptr, scale, x, 1.0);
     a.x_dir = dag ? +1 : -1;
-    a.xa = R(b * d + 1.0);
-    a.xb = R(c * d - 1.0);
-    a.xdd = R(d);
+    a.xa = R(xa);
+    a.xb = R(xb);
+    a.xdd = R(4.0 - M5);
     long mark = -1;
     if (ctx->timer.on) mark = timer_begin(ctx, hop_name(a, dag, pro && moebius, cfg));
     DWF_CHECK_LAUNCH(launch_hop<P>(a, dag, pro && moebius, cfg, ctx->stream));

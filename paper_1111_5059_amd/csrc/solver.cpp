@@ -328,7 +328,9 @@ int solve_full_5d(dwf_ctx* ctx, const dwf_params& p, const void* U64, const void
 }
 
 // one application of K (op 0: both 5D parities) or S (op 1: the even 5D parity; the odd part of
-// out is zero) in precision P on packed fields of that precision
+// out is zero) in precision P on packed fields of that precision.  K connects the 4D parities as D
+// does, K psi_q = S~ psi_q + 1/2 H psi_{1-q}, and needs no 5D fields: one hop per 4D parity with S~ on
+// its axpy operand (the Shamir D with xa = 0, xb = 1 and the other sign).
 template <typename P>
 static void dslash_5d_t(dwf_ctx* ctx, const dwf_params& p, const void* U, const void* in, void* out, int op,
                         bool dag) {
@@ -336,24 +338,33 @@ static void dslash_5d_t(dwf_ctx* ctx, const dwf_params& p, const void* U, const 
   const int Ls = p.Ls;
   const size_t hb = half_size<P>(g, Ls);
   hipStream_t s = ctx->stream;
+  Half<P> i4e = hview<P>(const_cast<void*>(in), g, Ls), i4o = hview<P>(reinterpret_cast<char*>(const_cast<void*>(in)) + hb, g, Ls);
+  Half<P> o4e = hview<P>(out, g, Ls), o4o = hview<P>(reinterpret_cast<char*>(out) + hb, g, Ls);
+  if (op == 0 && x_op_prec<P>()) {
+    Op<P> op4(ctx, g, p, U);
+    op4.hop_x(0, cv(i4o), o4e, dag, false, 0.5, cv(i4e), 0.0, 1.0);
+    op4.hop_x(1, cv(i4e), o4o, dag, false, 0.5, cv(i4o), 0.0, 1.0);
+    return;
+  }
   Op5<P> op5(ctx, g, p, U);
   const Geometry* gv = op5.g;
   const int LH = op5.Ls;
   const size_t fb = half_size<P>(gv, LH);
+  const Half<P> none5 = {nullptr, nullptr};
   auto field = [&](const char* name) { return hview<P>(ws_get(ctx, std::string("d5") + name, fb), gv, LH); };
-  Half<P> ie = field(".ie"), io = field(".io"), oe = field(".oe"), oo = field(".oo"), t = field(".t");
-  Half<P> i4e = hview<P>(const_cast<void*>(in), g, Ls), i4o = hview<P>(reinterpret_cast<char*>(const_cast<void*>(in)) + hb, g, Ls);
-  Half<P> o4e = hview<P>(out, g, Ls), o4o = hview<P>(reinterpret_cast<char*>(out) + hb, g, Ls);
-  DWF_CHECK_LAUNCH(launch_eo5_split<P>(i4e, i4o, ie, io, g->nsites, Ls, 0, s));
+  Half<P> ie = field(".ie"), oe = field(".oe"), t = field(".t");
   if (op == 0) {
+    Half<P> io = field(".io"), oo = field(".oo");
+    DWF_CHECK_LAUNCH(launch_eo5_split<P>(i4e, i4o, ie, io, g->nsites, Ls, 0, s));
     op5.K(0, cv(io), oe, dag, 0.5, 1.0);
     op5.K(1, cv(ie), oo, dag, 0.5, 1.0);
+    DWF_CHECK_LAUNCH(launch_eo5_split<P>(o4e, o4o, oe, oo, g->nsites, Ls, 1, s));
   } else {
-    if (dag) op5.mprec_dag(cv(ie), oe, t, oo);
+    DWF_CHECK_LAUNCH(launch_eo5_split<P>(i4e, i4o, ie, none5, g->nsites, Ls, 0, s));
+    if (dag) op5.mprec_dag(cv(ie), oe, t, none5);
     else op5.mprec(cv(ie), oe, t);
-    DWF_CHECK_LAUNCH(launch_zero(oo.data, fb, s));  // (the FP16 norms follow the data in the buffer)
+    DWF_CHECK_LAUNCH(launch_eo5_split<P>(o4e, o4o, oe, none5, g->nsites, Ls, 1, s));
   }
-  DWF_CHECK_LAUNCH(launch_eo5_split<P>(o4e, o4o, oe, oo, g->nsites, Ls, 1, s));
 }
 
 int dslash_5d(dwf_ctx* ctx, const dwf_params& p, const void* U, const void* in, void* out, int op, int dagger) {
