@@ -79,14 +79,14 @@ int pack_t(dwf_ctx* ctx, const dwf_params* p, int kind, const void* natural, voi
   const double2* nat = reinterpret_cast<const double2*>(natural);
   if (kind == DWF_KIND_GAUGE) {
     DWF_CHECK_LAUNCH(launch_pack_gauge<P>(t, nat, reinterpret_cast<typename P::S*>(packed), ctx->stream));
+  } else if (kind == DWF_KIND_FULL) {
+    char* base = reinterpret_cast<char*>(packed);
+    DWF_CHECK_LAUNCH(launch_pack_full<P>(t, p->Ls, nat, half_view<P>(base, g->nsites, p->Ls),
+                                         half_view<P>(base + half_bytes<P>(g->nsites, p->Ls), g->nsites, p->Ls),
+                                         ctx->stream));
   } else {
-    const size_t hb = half_bytes<P>(g->nsites, p->Ls);
-    for (int par = 0; par < 2; ++par) {
-      if (kind == DWF_KIND_EVEN && par == 1) continue;
-      if (kind == DWF_KIND_ODD && par == 0) continue;
-      char* base = reinterpret_cast<char*>(packed) + (kind == DWF_KIND_FULL && par == 1 ? hb : 0);
-      DWF_CHECK_LAUNCH(launch_pack_half<P>(t, par, p->Ls, nat, half_view<P>(base, g->nsites, p->Ls), ctx->stream));
-    }
+    DWF_CHECK_LAUNCH(launch_pack_half<P>(t, kind == DWF_KIND_ODD ? 1 : 0, p->Ls, nat,
+                                         half_view<P>(packed, g->nsites, p->Ls), ctx->stream));
   }
   return DWF_OK;
 }
@@ -97,12 +97,13 @@ int unpack_t(dwf_ctx* ctx, const dwf_params* p, int kind, const void* packed, vo
   const GeomTables t = g->tables();
   double2* nat = reinterpret_cast<double2*>(natural);
   const size_t hb = half_bytes<P>(g->nsites, p->Ls);
-  for (int par = 0; par < 2; ++par) {
-    if (kind == DWF_KIND_EVEN && par == 1) continue;
-    if (kind == DWF_KIND_ODD && par == 0) continue;
-    const char* base = reinterpret_cast<const char*>(packed) + (kind == DWF_KIND_FULL && par == 1 ? hb : 0);
-    DWF_CHECK_LAUNCH(launch_unpack_half<P>(t, par, p->Ls, chalf_view<P>(base, g->nsites, p->Ls), nat, ctx->stream));
-  }
+  if (kind == DWF_KIND_FULL)
+    DWF_CHECK_LAUNCH(launch_unpack_full<P>(t, p->Ls, chalf_view<P>(packed, g->nsites, p->Ls),
+                                           chalf_view<P>(reinterpret_cast<const char*>(packed) + hb, g->nsites, p->Ls),
+                                           nat, ctx->stream));
+  else
+    DWF_CHECK_LAUNCH(launch_unpack_half<P>(t, kind == DWF_KIND_ODD ? 1 : 0, p->Ls,
+                                           chalf_view<P>(packed, g->nsites, p->Ls), nat, ctx->stream));
   return DWF_OK;
 }
 

@@ -221,6 +221,11 @@ int launch_pack_half(const GeomTables& g, int parity, int Ls, const double2* nat
                      hipStream_t st);
 template <typename P>
 int launch_unpack_half(const GeomTables& g, int parity, int Ls, CHalf<P> in, double2* natural, hipStream_t st);
+// both parities of a full field
+template <typename P>
+int launch_pack_full(const GeomTables& g, int Ls, const double2* natural, Half<P> even, Half<P> odd, hipStream_t st);
+template <typename P>
+int launch_unpack_full(const GeomTables& g, int Ls, CHalf<P> even, CHalf<P> odd, double2* natural, hipStream_t st);
 template <typename Pi, typename Po>
 int launch_convert_links(const typename Pi::S* in, typename Po::S* out, long n, hipStream_t st);
 

@@ -76,3 +76,26 @@ def test_full_operator_and_input_factor(env, ora, Ls, prec, kind):
     ref = ora.hop5(po, U, ora.fifth(po, psio, "F"), out_parity=0)
     err = rel_err(lat.unpack_np(out, dwf.KIND_EVEN, P), ref)
     assert err < PREC_TOL[prec], ("HF", err)
+
+
+@pytest.mark.parametrize("Ls", [2, 15, 16, 17, 33])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16", "bf16"])
+def test_full_field_tiles(env, Ls, prec):
+    """Full fields are packed and unpacked in tiles of sites and 16 slices; a full pack holds bit for bit
+    what packing the even and odd halves (one thread per 5D site) gives, and unpacks to the same
+    values as the two halves."""
+    import torch
+    dwf, ctx = env
+    P = dwf.PREC_NAMES[prec]
+    for dims in ((2, 2, 2, 2), (6, 4, 2, 10)):
+        lat = dwf.Lattice(ctx, dims, Ls)
+        psi = synth.gaussian_spinor(dims, Ls, 880 + Ls)
+        psi[:, 0, 0, 0, 1] = 0.0  # (an FP16 site whose norm is that of zeros)
+        full, halves = lat.zeros(dwf.KIND_FULL, P), [lat.zeros(k, P) for k in (dwf.KIND_EVEN, dwf.KIND_ODD)]
+        src = lat.to_device(psi)
+        dwf.dwf_pack(ctx, lat.params(P), dwf.KIND_FULL, P, src, full)
+        for k, h in zip((dwf.KIND_EVEN, dwf.KIND_ODD), halves):
+            dwf.dwf_pack(ctx, lat.params(P), k, P, src, h)
+        assert torch.equal(full, torch.cat(halves))
+        both = lat.unpack(halves[0], dwf.KIND_EVEN, P) + lat.unpack(halves[1], dwf.KIND_ODD, P)
+        assert torch.equal(lat.unpack(full, dwf.KIND_FULL, P), both)
