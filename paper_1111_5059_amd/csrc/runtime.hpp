@@ -289,9 +289,11 @@ struct Op {
   // that of the arithmetic (FP64, FP32), else not at all (the 16-bit formats keep F in registers,
   // in the hop's prologue, so that it is not rounded).  The prologue triples the neighbour loads of
   // a hop that its gathers bound; F as a pass of its own is two streamed fields (FP64, Ls = 16, 24^3 x
-  // 64: prologue hop 2.1 ms, plain hop and pass 1.5 ms).  Returns whether tmp holds F in.
+  // 64: prologue hop 2.1 ms, plain hop and pass 1.5 ms).  Small fields keep the prologue: up to 32768
+  // 5D sites a hop waits for one round of loads at a time, and a launch costs more than wider loads.
+  // Returns whether tmp holds F in.
   bool input_factor(CHalf<P> in, Half<P> tmp) const {
-    if (!moebius || !tmp.data || sizeof(S) < 8) return false;
+    if (!moebius || !tmp.data || sizeof(S) < 8 || n5() <= 32768) return false;
     fifth(in, tmp, E_F);
     return true;
   }

@@ -38,16 +38,15 @@ def test_cyclic_recurrence(env, ora, Ls, prec, mass, M5):
         assert err < PREC_TOL[prec], (dag, err)
 
 
-@pytest.mark.parametrize("Ls", [2, 7, 16])
+@pytest.mark.parametrize("dims,Ls", [((4, 2, 6, 2), 2), ((4, 2, 6, 2), 7), ((4, 2, 6, 2), 16), ((8, 8, 8, 10), 14)])
 @pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16", "bf16"])
 @pytest.mark.parametrize("kind", ["shamir", "moebius", "sdep"])
-def test_full_operator_and_input_factor(env, ora, Ls, prec, kind):
+def test_full_operator_and_input_factor(env, ora, dims, Ls, prec, kind):
     """D and D^dag with A applied to the hop's axpy operand (both chiralities' boundaries, odd and
     smallest extents, coefficients per slice), and H F and M_prec with the input factor in a pass of
-    its own (FP64, FP32) or in the hop (16-bit)."""
+    its own (FP64, FP32, the last lattice) or in the hop (16-bit, and the small ones)."""
     dwf, ctx = env
     P = dwf.PREC_NAMES[prec]
-    dims = (4, 2, 6, 2)
     kw, okw = {}, {}
     if kind == "moebius":
         kw = okw = {"b": 1.5, "c": 0.5}
