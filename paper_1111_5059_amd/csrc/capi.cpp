@@ -535,6 +535,7 @@ int dwf_tune_set(dwf_ctx* ctx, int kernel_id, int prec, int Ls, int spb, int ns,
   c.xcd = xcd ? 1 : 0;
   c.ll = ll == 1 ? 1 : 0;
   c.stage = ll == 2 ? 1 : 0;
+  c.tuned = 1;
   ctx->tune[key] = c;
   return DWF_OK;
 }

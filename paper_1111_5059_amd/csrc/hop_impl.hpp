@@ -47,6 +47,25 @@ inline size_t hop_lds_bytes(const LaunchCfg& cfg, int Ls, bool epi) {
   return b;
 }
 
+// one slice of the per-chirality matrix product along s, from a site's 12 rows in LDS
+template <typename R>
+__device__ __forceinline__ void dense_result(const cx<R>* rows, int stride, int s, int Ls, const R* E, cx<R> o[12]) {
+  const R* E0 = E + s * Ls;
+  const R* E1 = E + Ls * Ls + s * Ls;
+#pragma unroll
+  for (int k = 0; k < 12; ++k) o[k] = {R(0), R(0)};
+  for (int sp = 0; sp < Ls; ++sp) {
+    const R e0 = E0[sp], e1 = E1[sp];
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      const cx<R> v = rows[k * stride + sp];
+      const R e = k < 6 ? e0 : e1;
+      o[k].re = fma(e, v.re, o[k].re);
+      o[k].im = fma(e, v.im, o[k].im);
+    }
+  }
+}
+
 // Moebius prologue of one slice s: the hop's input becomes b_s psi_s + u P+ psi_{s-1} +
 // l P- psi_{s+1} (F = b + c S~ with the -m wrap at the ends of the fifth dimension).  The
 // coefficients depend on s only; they are formed once per thread, before the direction loop,
@@ -787,6 +806,175 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
   }
 }
 
+// ------------------------------------------------------------------ small fields
+// A hop on a few hundred workgroups or fewer leaves most of the chip idle, and its time is the chain of one
+// thread: site, neighbour index, links, then one round of loads after the other for the eight
+// directions, each a miss to memory (another XCD wrote the field; 10-13 us on 4^4 x 8 whatever the
+// precision).  Here the four waves of a workgroup take the same 64 (site, slice) lanes, wave mu the
+// two neighbours in direction mu, and the partial results are added through LDS (18 KB in FP32, 36 KB
+// in FP64); the first wave applies the epilogue, the axpy and the CG step, whose operands it reads
+// beside the gathers.  Sites in x_cb order, links from memory.
+// (The scheduling barrier keeps both neighbours' and both links' loads ahead of the arithmetic: one
+// round of memory latency instead of two.)
+template <int MU, bool DAG, bool PRO, typename P>
+__device__ __forceinline__ void split_dirs(const HopArgs<P>& a, long x, int s, const ProCoef<typename P::R> (&pro)[1],
+                                           cx<typename P::R> (&acc)[1][12]) {
+  using R = typename P::R;
+  constexpr int SF = DAG ? +1 : -1;  // forward: 1 - g (H), 1 + g (H^dag); backward the opposite
+  const int* nb = a.nbr + x * 8;
+  const long yf = nb[MU], yb = nb[MU + 4];
+  const typename P::S* L = a.links + x * 72 + MU * 9;
+  if constexpr (std::is_same<P, P16>::value) {
+    F16In<1> f, b;
+    __half2 u[2][9];
+#pragma unroll
+    for (int e = 0; e < 9; ++e) {
+      u[0][e] = L[e];
+      u[1][e] = L[36 + e];
+    }
+    load_dir_f16<1, PRO>(a, yf, s, a.Ls, pro, f);
+    load_dir_f16<1, PRO>(a, yb, s, a.Ls, pro, b);
+    __builtin_amdgcn_sched_barrier(0);
+    apply_dir_f16<MU, SF, 1, false>(a, u[0], 0, f, acc);
+    apply_dir_f16<MU, -SF, 1, false>(a, u[1], 0, b, acc);
+  } else {
+    typename P::S u[2][9];
+#pragma unroll
+    for (int e = 0; e < 9; ++e) {
+      u[0][e] = L[e];
+      u[1][e] = L[36 + e];
+    }
+    cx<R> pf[12], pb[12], U[9], h[6], v[6];
+    load_input<P, PRO>(a, yf, s, pro[0], pf);
+    load_input<P, PRO>(a, yb, s, pro[0], pb);
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int e = 0; e < 9; ++e) U[e] = P::ld(u[0][e]);
+    project<MU, SF>(pf, h);
+    su3_mul_half(U, h, v);
+    reconstruct_acc<MU, SF>(v, acc[0]);
+#pragma unroll
+    for (int e = 0; e < 9; ++e) U[e] = P::ld(u[1][e]);
+    project<MU, -SF>(pb, h);
+    su3_mul_half(U, h, v);
+    reconstruct_acc<MU, -SF>(v, acc[0]);
+  }
+}
+
+template <typename P, int LS, bool DAG, bool PRO, int EPI, bool CG>
+__device__ __forceinline__ void hop_split_body(const HopArgs<P>& a, long bid, int spb) {
+  using R = typename P::R;
+  extern __shared__ __align__(16) unsigned char smem_raw[];
+  R* part = reinterpret_cast<R*>(smem_raw);  // [wave - 1][24][lane]
+  const int Ls = LS > 0 ? LS : a.Ls;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lsite = lane / Ls, s = lane - lsite * Ls;
+  const long x0 = bid * spb + lsite;
+  const bool active = lsite < spb && x0 < a.nsites;
+  const long x = active ? x0 : 0;
+  cx<R> acc[1][12];
+#pragma unroll
+  for (int k = 0; k < 12; ++k) acc[0][k] = {R(0), R(0)};
+  // the first wave's operands on its own sites, read beside the gathers
+  constexpr bool XOP = x_op_prec<P>() && !CG && EPI == 0;
+  const bool x_plain = a.x.data && !(XOP && a.x_dir);
+  cx<R> xv[12], rv[CG ? 12 : 1];
+  if (w == 0 && active) {
+    if (x_plain) load_spinor<P>(a.x, x, s, Ls, xv);
+    if constexpr (CG) load_spinor<P>(CHalf<P>{a.cg_r.data, a.cg_r.norm}, x, s, Ls, rv);
+  }
+  if (active) {
+    HopArgs<P> ak = a;
+    ak.Ls = Ls;
+    const ProCoef<R> pro[1] = {pro_coef<P, PRO>(ak, s)};
+    switch (w) {
+      case 0: split_dirs<0, DAG, PRO>(ak, x, s, pro, acc); break;
+      case 1: split_dirs<1, DAG, PRO>(ak, x, s, pro, acc); break;
+      case 2: split_dirs<2, DAG, PRO>(ak, x, s, pro, acc); break;
+      default: split_dirs<3, DAG, PRO>(ak, x, s, pro, acc); break;
+    }
+  }
+  if (w != 0) {
+    R* mine = part + (w - 1) * 24 * 64 + lane;
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      mine[(2 * k) * 64] = acc[0][k].re;
+      mine[(2 * k + 1) * 64] = acc[0][k].im;
+    }
+  }
+  __syncthreads();
+  if (w != 0) return;
+#pragma unroll
+  for (int v = 0; v < 3; ++v)
+#pragma unroll
+    for (int k = 0; k < 12; ++k) {
+      const R* theirs = part + (v * 24 + 2 * k) * 64 + lane;
+      acc[0][k] = {acc[0][k].re + theirs[0], acc[0][k].im + theirs[64]};
+    }
+  if constexpr (!std::is_same<P, P16>::value) {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) acc[0][k] = a.scale * acc[0][k];
+  }
+  if constexpr (EPI >= 2) fifth_scan_apply<(LS > 0 ? LS : 1)>(acc[0], s, a.es);
+  if constexpr (EPI == 1) {
+    // dense matrices along s through LDS (this wave's own accesses, in order)
+    cx<R>* rows = reinterpret_cast<cx<R>*>(smem_raw) + lsite * 12 * Ls;
+    if (active) {
+#pragma unroll
+      for (int k = 0; k < 12; ++k) rows[k * Ls + s] = acc[0][k];
+    }
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+    if (active) dense_result<R>(rows, Ls, s, Ls, a.E, acc[0]);
+  }
+  constexpr bool XS = CG && !std::is_same<P, P64>::value && (LS == 8 || LS == 16 || LS == 32);
+  double nrm = 0.0;
+  if (active) {
+    if constexpr (XOP) {
+      if (a.x_dir) axpy_x_op<P>(a, x, s, Ls, acc[0]);
+    }
+    if (x_plain) {
+      if constexpr (XS) {
+        if (a.x_es2) fifth_bidiagonal_apply<(LS > 0 ? LS : 1)>(xv, s, a.es2);
+      }
+#pragma unroll
+      for (int k = 0; k < 12; ++k) acc[0][k] = acc[0][k] + a.ax * xv[k];
+    }
+    if constexpr (CG) {
+      const R alpha = R(a.cg_scalars[S_ALPHA]);
+#pragma unroll
+      for (int k = 0; k < 12; ++k) {
+        rv[k] = {rv[k].re - alpha * acc[0][k].re, rv[k].im - alpha * acc[0][k].im};
+        nrm += double(rv[k].re) * double(rv[k].re) + double(rv[k].im) * double(rv[k].im);
+      }
+      store_spinor<P>(a.cg_r, x, s, Ls, rv);
+    } else {
+#pragma unroll
+      for (int k = 0; k < 12; ++k)
+        nrm += double(acc[0][k].re) * double(acc[0][k].re) + double(acc[0][k].im) * double(acc[0][k].im);
+      if (a.out.data) store_spinor<P>(a.out, x, s, Ls, acc[0]);
+    }
+  }
+  if constexpr (EPI == 3 && !CG) {
+    fifth_scan_apply<(LS > 0 ? LS : 1)>(acc[0], s, a.es2);
+    if (active) store_spinor<P>(a.out2, x, s, Ls, acc[0]);
+  }
+  if (a.norm_partials) {
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) nrm += __shfl_down(nrm, off, 64);
+    if (lane == 0) a.norm_partials[bid] = nrm;
+  }
+}
+
+// (the overload of the small fields, a kernel of its own: inside the general one it raised the FP64
+// scan hops from 160 to 190 registers)
+template <typename P, int LS, int NS, bool DAG, bool PRO, int EPI, bool LL, bool CG, bool ST>
+__global__ void __launch_bounds__(256) hop_kernel(HopArgs<P> a, int spb) {
+  static_assert(NS == 1 && !ST, "small fields: one slice per lane, no staged neighbours");
+  hop_split_body<P, LS, DAG, PRO, EPI, CG>(a, blockIdx.x, spb);
+}
+
 template <typename P, int LS, int NS, bool DAG, bool PRO, int EPI, bool LL, bool CG, bool ST>
 __global__ void __launch_bounds__(256, (hop_min_waves<P, NS, EPI, CG>())) hop_kernel(HopArgs<P> a, int spb, int xcd) {
   const long bid = xcd ? xcd_block(blockIdx.x, gridDim.x) : (long)blockIdx.x;
@@ -930,22 +1118,29 @@ static int launch_hop_t(const HopArgs<P>& a, const LaunchCfg& cfg, hipStream_t s
       return -1;
     }
   }
+  if constexpr (NS == 1) {
+    constexpr bool LL = !std::is_same<P, P16>::value;
+    if (split_shape<P>(cfg, a.nsites, a.Ls)) {
+      const int sp = split_spb(a.Ls);
+      void (*k)(HopArgs<P>, int) = hop_kernel<P, LS, NS, DAG, PRO, EPI, LL, CG, false>;
+      hipLaunchKernelGGL(k, dim3((unsigned)((a.nsites + sp - 1) / sp)), dim3(256), 3 * 24 * 64 * sizeof(typename P::R), st,
+                         a, sp);
+      return hipGetLastError() == hipSuccess ? 0 : -2;
+    }
+  }
   if constexpr (stage_capable<P, LS, NS, PRO, EPI>()) {
     if (stage_shape(cfg, a.Ls)) {
       LaunchCfg c2 = cfg;
       c2.ll = 1;
-      hipLaunchKernelGGL((hop_kernel<P, LS, NS, DAG, PRO, EPI, true, CG, true>), dim3((unsigned)blocks),
-                         dim3(threads), hop_lds_bytes<P>(c2, a.Ls, false), st, a, cfg.spb, cfg.xcd);
+      void (*k)(HopArgs<P>, int, int) = hop_kernel<P, LS, NS, DAG, PRO, EPI, true, CG, true>;
+      hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(threads), hop_lds_bytes<P>(c2, a.Ls, false), st, a, cfg.spb, cfg.xcd);
       return hipGetLastError() == hipSuccess ? 0 : -2;
     }
   }
   const size_t lds = hop_lds_bytes<P>(cfg, a.Ls, EPI == 1);
-  if (cfg.ll)
-    hipLaunchKernelGGL((hop_kernel<P, LS, NS, DAG, PRO, EPI, true, CG, false>), dim3((unsigned)blocks), dim3(threads),
-                       lds, st, a, cfg.spb, cfg.xcd);
-  else
-    hipLaunchKernelGGL((hop_kernel<P, LS, NS, DAG, PRO, EPI, false, CG, false>), dim3((unsigned)blocks),
-                       dim3(threads), lds, st, a, cfg.spb, cfg.xcd);
+  void (*k1)(HopArgs<P>, int, int) = hop_kernel<P, LS, NS, DAG, PRO, EPI, true, CG, false>;
+  void (*k0)(HopArgs<P>, int, int) = hop_kernel<P, LS, NS, DAG, PRO, EPI, false, CG, false>;
+  hipLaunchKernelGGL(cfg.ll ? k1 : k0, dim3((unsigned)blocks), dim3(threads), lds, st, a, cfg.spb, cfg.xcd);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 

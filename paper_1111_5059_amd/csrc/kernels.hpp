@@ -92,11 +92,24 @@ struct LaunchCfg {
   int ll;         // links staged in LDS
   int stage = 0;  // neighbour spinors (and links) staged through LDS (FP16, Ls 8/16/32, spb = 256/Ls, ns 1)
   int off = 0;    // (the interleaved batched hop's entry) interleaving switched off
+  int tuned = 0;  // set by the caller, not the default: taken as it is at every size
 };
 // the launch shape the LDS-staged hop runs with
 inline bool stage_shape(const LaunchCfg& cfg, int Ls) {
   return cfg.stage && cfg.ns == 1 && cfg.spb * Ls == 256 && (Ls == 8 || Ls == 16 || Ls == 32);
 }
+
+// Small fields run the hop with its eight directions spread over the four waves of a workgroup
+// (see hop_split_body): default launch shapes, a site's slices in one wave, and at most as many 5D
+// sites as it was faster for (M_prec, us, general / spread: FP32 n5 = 65536 19.7 / 18.7, 131072 29.8 /
+// 29.0; FP64 49152 27.8 / 25.6, 65536 30.6 / 31.4; FP16 32768 11.9 / 10.3, 65536 12.7 / 14.9).
+template <typename P>
+bool split_shape(const LaunchCfg& cfg, long nsites, int Ls) {
+  const long most = sizeof(typename P::S) == 4 ? 32768 : sizeof(typename P::S) == 8 ? 65536 : 49152;
+  return !cfg.tuned && cfg.ns == 1 && !cfg.stage && Ls <= 64 && nsites * Ls <= most;
+}
+// its sites per workgroup
+inline int split_spb(int Ls) { return 64 / Ls; }
 
 // the launches that apply a site-local operator to the fused CG step's axpy operand
 // (HopArgs::x_es2): one slice per lane, the site's Ls lanes a wave segment, not the LDS-staged

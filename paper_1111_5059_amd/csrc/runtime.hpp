@@ -327,7 +327,10 @@ struct Op {
   // ... and the last hop of M^dag q can rebuild q from that second output (q need not be stored)
   bool rebuild_q_ok() const { return second_output_ok() && x_es2_shape<P>(cfg, Ls); }
   // workgroups of one hop launch (the norm partials it writes)
-  long hop_blocks() const { return (g->nsites + cfg.spb - 1) / cfg.spb; }
+  long hop_blocks() const {
+    const int spb = split_shape<P>(cfg, g->nsites, Ls) ? split_spb(Ls) : cfg.spb;
+    return (g->nsites + spb - 1) / spb;
+  }
   // M_prec psi = psi - 1/4 A^-1 H_oe (F A^-1) H_eo F psi    (odd -> odd); tmp_f (optional, Moebius):
   // room for F psi (see input_factor);
   // ainvdag_out (optional, see second_output_ok): also A^-dag (M_prec psi); with it, out may be
