@@ -63,11 +63,15 @@ __global__ void __launch_bounds__(RED_THREADS) dot_kernel(CHalf<P> a, CHalf<P> b
   }
 }
 
-// One workgroup of 1024 threads; each thread keeps four independent partial sums (loads in
-// flight) over a fixed set of indices, combined in a fixed order: deterministic.
+// One workgroup of 1024 threads (256 for few partials) per set of scalars; each thread keeps four
+// independent partial sums (loads in flight) over a fixed set of indices, combined in a fixed order:
+// deterministic.  host (optional): the sum is also stored there, one 64-bit store per set that the host
+// polls (see wait_host), so that no copy and no stream synchronisation follow.
 __global__ void __launch_bounds__(1024) reduce_kernel(const double* partials, int n, int ncomp, double* scalars,
-                                                       int slot, int mode, int hist) {
+                                                       int slot, int mode, int hist, long pstride, double* host) {
   __shared__ double red[16];
+  partials += blockIdx.x * pstride;
+  scalars += blockIdx.x * S_COUNT;
   for (int c = 0; c < ncomp; ++c) {
     double a0 = 0.0, a1 = 0.0, a2 = 0.0, a3 = 0.0;
     const int stride = blockDim.x;
@@ -82,6 +86,7 @@ __global__ void __launch_bounds__(1024) reduce_kernel(const double* partials, in
     const double t = block_sum((a0 + a1) + (a2 + a3), red);
     __syncthreads();
     if (threadIdx.x == 0) {
+      if (host) __hip_atomic_store(host + blockIdx.x, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
       scalars[slot + c] = t;
       if (mode == 1) {
         // alpha = rr / qq
@@ -97,9 +102,10 @@ __global__ void __launch_bounds__(1024) reduce_kernel(const double* partials, in
 }
 
 int launch_reduce(const double* partials, int n, int ncomp, double* scalars, int slot, int mode, hipStream_t st,
-                  int hist) {
-  if (hist >= XFLUSH_MAX) return -1;
-  hipLaunchKernelGGL(reduce_kernel, dim3(1), dim3(1024), 0, st, partials, n, ncomp, scalars, slot, mode, hist);
+                  int hist, int sets, long pstride, double* host) {
+  if (hist >= XFLUSH_MAX || sets < 1 || (sets > 1 && pstride < n) || (host && ncomp != 1)) return -1;
+  hipLaunchKernelGGL(reduce_kernel, dim3(sets), dim3(n <= 1024 ? 256 : 1024), 0, st, partials, n, ncomp, scalars, slot,
+                     mode, hist, pstride, host);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 
@@ -181,7 +187,8 @@ __global__ void __launch_bounds__(256) cg_pupdate_kernel(CHalf<P> r, CHalf<P> pi
                                                           double* scalars, double rr_new, long n5, int Ls) {
   using R = typename P::R;
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) scalars[S_RR] = rr_new;
+  if (beta < 0.0) beta = scalars[S_BETA];
+  else if (i == 0) scalars[S_RR] = rr_new;
   if (i >= n5) return;
   const long xs = i / Ls;
   const int s = int(i - xs * Ls);
@@ -262,7 +269,8 @@ __global__ void __launch_bounds__(256) cg_pupdate_f_kernel(CHalf<P> r, CHalf<P> 
                                                             const typename P::R* bs, const typename P::R* cs) {
   using R = typename P::R;
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) scalars[S_RR] = rr_new;
+  if (beta < 0.0) beta = scalars[S_BETA];
+  else if (i == 0) scalars[S_RR] = rr_new;
   if (i >= n5) return;
   const long xs = i / Ls;
   const int s = int(i - xs * Ls);
@@ -476,19 +484,19 @@ int launch_accumulate(Half<P64> hi, Half<Px> lo, long n5, int Ls, hipStream_t st
 // r * RS + s of a field of extent LT = nrhs * RS (one thread per 5D site of the whole field).
 
 // p_out = r + beta_k p_in with beta_k = coef[k] of the slice's right-hand side k (0: p_in unread);
-// the first threads also record |r_k|^2 = coef[K + k] at scalars[k S_COUNT + S_RR]
+// the first threads also record |r_k|^2 = coef[K + k] at scalars[k S_COUNT + S_RR].  coef == nullptr:
+// beta_k = scalars[k S_COUNT + S_BETA], and S_RR is left as the reduction set it
 template <typename P>
 __global__ void __launch_bounds__(256) ilv_pupdate_kernel(CHalf<P> r, CHalf<P> pin, Half<P> pout, const double* coef,
                                                            double* scalars, long n5, int LT, int RS) {
   using R = typename P::R;
   const long i = (long)blockIdx.x * blockDim.x + threadIdx.x;
   const int K = LT / RS;
-  if (i < K) scalars[i * S_COUNT + S_RR] = coef[K + i];
+  if (coef && i < K) scalars[i * S_COUNT + S_RR] = coef[K + i];
   if (i >= n5) return;
-  const double* betas = coef;
   const long xs = i / LT;
   const int s = int(i - xs * LT);
-  const double beta = betas[s / RS];
+  const double beta = coef ? coef[s / RS] : scalars[(s / RS) * S_COUNT + S_BETA];
   cx<R> rv[12], pv[12];
   load_spinor<P>(r, xs, s, LT, rv);
   if (beta != 0.0) {

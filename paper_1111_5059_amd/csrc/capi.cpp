@@ -201,6 +201,8 @@ int dwf_ctx_create(dwf_ctx** out, void* stream) {
     DWF_CHECK_HIP(hipGetDevice(&c->device));
     scratch_init();  // device address of the no-allocation entry point's array on this device
     DWF_CHECK_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->h_scalars), S_COUNT * sizeof(double)));
+    DWF_CHECK_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->h_poll), HOST_POLL * sizeof(double),
+                                hipHostMallocCoherent | hipHostMallocMapped));
     *out = c.release();
     return DWF_OK;
   });
@@ -215,6 +217,7 @@ int dwf_ctx_destroy(dwf_ctx* ctx) {
     ctx->geoms.clear();
     timer_release(ctx);
     if (ctx->h_scalars) (void)hipHostFree(ctx->h_scalars);
+    if (ctx->h_poll) (void)hipHostFree(ctx->h_poll);
     delete ctx;
     return DWF_OK;
   });

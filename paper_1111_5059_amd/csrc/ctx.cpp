@@ -33,6 +33,35 @@ double read_scalar(dwf_ctx* ctx, const double* dscalars, int slot) {
   return ctx->h_scalars[slot];
 }
 
+// a NaN that no reduction produces (a sum that is this NaN ends the wait with an error, as any NaN does)
+static constexpr uint64_t UNWRITTEN = 0xfff8dead0000beefULL;
+
+void arm_host(dwf_ctx* ctx, int n) {
+  volatile uint64_t* p = reinterpret_cast<volatile uint64_t*>(ctx->h_poll);
+  for (int k = 0; k < n; ++k) p[k] = UNWRITTEN;
+}
+
+double wait_host(dwf_ctx* ctx, int k) {
+  const volatile uint64_t* p = reinterpret_cast<const volatile uint64_t*>(ctx->h_poll) + k;
+  uint64_t v = *p;
+  for (long n = 1; v == UNWRITTEN; ++n) {
+    if ((n & 0xfff) == 0) {  // a few tens of microseconds: has the stream ended, or failed?
+      const hipError_t e = hipStreamQuery(ctx->stream);
+      if (e == hipErrorNotReady) (void)hipGetLastError();  // (not an error for the next launch's check)
+      v = *p;
+      if (e == hipSuccess && v == UNWRITTEN) throw Error{DWF_ERR_NAN, "the residual of an iteration was not written"};
+      if (e != hipSuccess && e != hipErrorNotReady)
+        throw Error{DWF_ERR_HIP, std::string("CG iteration: ") + hipGetErrorString(e)};
+    } else {
+      __builtin_ia32_pause();
+      v = *p;
+    }
+  }
+  double d;
+  std::memcpy(&d, &v, sizeof(d));
+  return d;
+}
+
 long timer_begin(dwf_ctx* ctx, const std::string& kernel) {
   KernelTimer& t = ctx->timer;
   if (!t.on) return -1;

@@ -170,8 +170,10 @@ constexpr int XFLUSH_MAX = S_COUNT - S_AHIST;
 // dst[slot] = sum(partials[0..n)) and the CG scalar update selected by mode:
 //   0: just store;  1: alpha = rr/qq (slot = S_QQ), also stored at S_AHIST + hist when hist >= 0;
 //   2: beta = rrnew/rr, rr = rrnew (slot = S_RRNEW)
+// sets > 1: the same for that many sets of partials (pstride apart) and scalars (S_COUNT apart), in one
+// launch; host (ncomp 1): the sums also to host[set], memory the host can poll
 int launch_reduce(const double* partials, int n, int ncomp, double* scalars, int slot, int mode, hipStream_t st,
-                  int hist = -1);
+                  int hist = -1, int sets = 1, long pstride = 0, double* host = nullptr);
 // pending CG directions: x += sum_j scalars[S_AHIST + slot[j]] p[j], j < n
 template <typename P>
 struct XFlush {
@@ -181,7 +183,9 @@ struct XFlush {
 };
 template <typename P, typename Px>
 int launch_xflush(Half<Px> x, const XFlush<P>& f, const double* scalars, long n5, int Ls, hipStream_t st);
-// p_out = r + beta p_in (p_in unused when beta = 0; it may be p_out) and scalars[S_RR] = rr_new
+// p_out = r + beta p_in (p_in unused when beta = 0; it may be p_out) and scalars[S_RR] = rr_new; with
+// BETA_ON_DEVICE as beta: scalars[S_BETA], and S_RR is left as the reduction (mode 2) set it
+constexpr double BETA_ON_DEVICE = -1.0;  // (beta is a quotient of squared norms, never negative)
 template <typename P>
 int launch_cg_pupdate(CHalf<P> r, CHalf<P> pin, Half<P> pout, double beta, double* scalars, double rr_new, long n5,
                       int Ls, hipStream_t st);
@@ -202,7 +206,7 @@ int launch_zero(void* p, size_t bytes, hipStream_t st);
 // Fields of several right-hand sides interleaved along s: slice s of right-hand side r is slice
 // r RS + s of a field of extent LT (a separate field: r = 0, LT = RS).
 // p_out = r + coef[k] p_in per right-hand side k (device table; 0: p_in unread), and
-// scalars[k S_COUNT + S_RR] = coef[K + k] (K = LT / RS)
+// scalars[k S_COUNT + S_RR] = coef[K + k] (K = LT / RS); coef == nullptr: beta_k from S_BETA
 template <typename P>
 int launch_ilv_pupdate(CHalf<P> r, CHalf<P> pin, Half<P> pout, const double* coef, double* scalars, long nsites, int LT,
                        int RS, hipStream_t st);

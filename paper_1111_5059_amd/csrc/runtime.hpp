@@ -92,6 +92,7 @@ struct dwf_ctx {
   std::map<std::string, std::pair<void*, size_t>> emats;  // fifth-dimension matrices by key
   std::map<long long, dwf::LaunchCfg> tune;              // (prec, Ls) -> hop launch configuration
   double* h_scalars = nullptr;                           // pinned host mirror of the CG scalars
+  double* h_poll = nullptr;                              // pinned: residuals the device stores, the host polls
   dwf::KernelTimer timer;
 };
 
@@ -121,6 +122,12 @@ LaunchCfg ilv_config(dwf_ctx* ctx, int prec, int Ls);
 const void* fifth_matrices(dwf_ctx* ctx, int Ls, double M5, double m, double b, double c, int prec,
                            const double* bs = nullptr, const double* cs = nullptr);
 double read_scalar(dwf_ctx* ctx, const double* dscalars, int slot);
+// Values that a reduction stores in host memory: arm_host marks the first n slots of ctx->h_poll unwritten
+// (before the launch), wait_host spins until slot k is written and returns it.  The wait ends when
+// the stream has nothing left to run, with an error if the value is still missing then.
+constexpr int HOST_POLL = 64;
+void arm_host(dwf_ctx* ctx, int n);
+double wait_host(dwf_ctx* ctx, int k);
 // timer marks around one launch (no-ops while timing is off); begin returns the mark index or -1
 long timer_begin(dwf_ctx* ctx, const std::string& kernel);
 void timer_end(dwf_ctx* ctx, long mark, double bytes);

@@ -133,7 +133,7 @@ static int cg_normal(dwf_ctx* ctx, const OpT<P64>& op64, const OpT<Pi>& opi, CHa
   const bool PRE = opi.moebius;
   Half<Pi> fp = PRE ? hview<Pi>(ws_get(ctx, tag + ".fp." + pname(Pi::ID), hbi), g, Ls) : Half<Pi>{nullptr, nullptr};
   // the new direction goes to the next ring slot: never a pending one, since at most KX - 1
-  // are pending here, the last of them the current one
+  // are pending here, the last of them the current one (it becomes the current one when cur advances)
   auto p_update = [&](double beta, double rr_new) {
     const int nxt = (cur + 1) % KX;
     if (PRE) {
@@ -143,10 +143,10 @@ static int cg_normal(dwf_ctx* ctx, const OpT<P64>& op64, const OpT<Pi>& opi, CHa
     } else {
       DWF_CHECK_LAUNCH(launch_cg_pupdate<Pi>(cv(r), cv(pr[cur]), pr[nxt], beta, sc, rr_new, n5, Ls, s));
     }
-    cur = nxt;
   };
   // p = r
   p_update(0.0, rr);
+  cur = (cur + 1) % KX;
   double rr_max = rr, rr_true = rr;
   const long nb_hop = opi.hop_blocks();
   int it = 0;
@@ -164,9 +164,13 @@ static int cg_normal(dwf_ctx* ctx, const OpT<P64>& op64, const OpT<Pi>& opi, CHa
     ++pend.n;
     // r -= alpha M^dag q and |r|^2, fused into the last hop of M^dag q
     opi.mprec_dag_cg(cv(q), to, te, r, sc, part, OUT2, QREB);
-    DWF_CHECK_LAUNCH(launch_reduce(part, int(nb_hop), 1, sc, S_RRNEW, 0, s));
+    arm_host(ctx, 1);
+    DWF_CHECK_LAUNCH(launch_reduce(part, int(nb_hop), 1, sc, S_RRNEW, 2, s, -1, 1, 0, ctx->h_poll));
     if (pend.n == KX) flush();
-    double rr_new = read_scalar(ctx, sc, S_RRNEW);
+    // the next direction with beta = rr_new / rr from the device, queued before the host has read rr_new:
+    // the read hides behind it.  (Where the host decides otherwise, the slot is written again.)
+    p_update(BETA_ON_DEVICE, 0.0);
+    double rr_new = wait_host(ctx, 0);
     ++it;
     if (!std::isfinite(rr_new)) throw Error{DWF_ERR_NAN, "non-finite residual in CG iteration"};
     // reliable update when the iterated residual has dropped by delta since the last one,
@@ -182,11 +186,14 @@ static int cg_normal(dwf_ctx* ctx, const OpT<P64>& op64, const OpT<Pi>& opi, CHa
       rr_max = rr_new;
       rr_true = rr_new;
       st->reliable_updates++;
-      if (rr_new > target && (RESTART || diverging)) {
+      // (the direction once more, from the recomputed residual)
+      const bool restart = rr_new > target && (RESTART || diverging);
+      if (rr_new > target) p_update(restart ? 0.0 : rr_new / rr, rr_new);
+      if (restart) {
         // BF16 (8-bit mantissa): the retained direction loses conjugacy and CG stagnates;
         // restart the Krylov space from the recomputed residual.
-        p_update(0.0, rr_new);
         rr = rr_new;
+        cur = (cur + 1) % KX;
         continue;
       }
     }
@@ -194,8 +201,7 @@ static int cg_normal(dwf_ctx* ctx, const OpT<P64>& op64, const OpT<Pi>& opi, CHa
       rr = rr_new;
       break;
     }
-    const double beta = rr_new / rr;
-    p_update(beta, rr_new);
+    cur = (cur + 1) % KX;
     rr = rr_new;
     if (rr > rr_max) rr_max = rr;
   }
@@ -516,21 +522,19 @@ static void cg_batched_ilv(dwf_ctx* ctx, std::vector<BatchSys*> sys, double delt
   // the fifth-dimension tables per right-hand side: A^-1, A^-dag, A^-dag (F^dag), A^dag
   const size_t nscan = size_t(4) * K0;
   FifthScan<R>* dscan = reinterpret_cast<FifthScan<R>*>(ws_get(ctx, "ilv.scan", nscan * sizeof(FifthScan<R>)));
-  // pinned host mirrors: scalars, p-update coefficients, fifth-dimension tables (freed on every
+  // pinned host mirrors: p-update coefficients, fifth-dimension tables (freed on every
   // exit, also when a later allocation throws)
   struct HostFree {
-    void* p[3] = {nullptr, nullptr, nullptr};
+    void* p[2] = {nullptr, nullptr};
     ~HostFree() {
       for (void* q : p)
         if (q) (void)hipHostFree(q);
     }
   } host_free;
-  DWF_CHECK_HIP(hipHostMalloc(&host_free.p[0], size_t(K0) * S_COUNT * sizeof(double)));
-  DWF_CHECK_HIP(hipHostMalloc(&host_free.p[1], size_t(2) * K0 * sizeof(double)));
-  DWF_CHECK_HIP(hipHostMalloc(&host_free.p[2], nscan * sizeof(FifthScan<R>)));
-  double* hsc = static_cast<double*>(host_free.p[0]);
-  double* hcoef = static_cast<double*>(host_free.p[1]);
-  FifthScan<R>* hscan = static_cast<FifthScan<R>*>(host_free.p[2]);
+  DWF_CHECK_HIP(hipHostMalloc(&host_free.p[0], size_t(2) * K0 * sizeof(double)));
+  DWF_CHECK_HIP(hipHostMalloc(&host_free.p[1], nscan * sizeof(FifthScan<R>)));
+  double* hcoef = static_cast<double*>(host_free.p[0]);
+  FifthScan<R>* hscan = static_cast<FifthScan<R>*>(host_free.p[1]);
   // interleaved inner vectors (sized for all K0 right-hand sides)
   const size_t hbi = half_bytes<Pi>(ns, LT0);
   void* rb = ws_get(ctx, "ilv.r", hbi);
@@ -616,6 +620,11 @@ static void cg_batched_ilv(dwf_ctx* ctx, std::vector<BatchSys*> sys, double delt
     const int nxt = (cur + 1) % KX;
     DWF_CHECK_LAUNCH(launch_ilv_pupdate<Pi>(cv(H(rb, LT)), cv(H(pb[cur], LT)), H(pb[nxt], LT), dcoef, sc, ns, LT, RS, s));
     cur = nxt;
+  };
+  // the same with every beta from the device (the reductions' S_BETA); cur does not advance
+  auto p_update_ahead = [&]() {
+    const int nxt = (cur + 1) % KX;
+    DWF_CHECK_LAUNCH(launch_ilv_pupdate<Pi>(cv(H(rb, LT)), cv(H(pb[cur], LT)), H(pb[nxt], LT), nullptr, sc, ns, LT, RS, s));
   };
   auto flush = [&]() {
     DWF_CHECK_LAUNCH((launch_ilv_xflush<Pi, PX>(HX(xlb, LT), pend, sc, ns, LT, RS, s)));
@@ -718,24 +727,22 @@ static void cg_batched_ilv(dwf_ctx* ctx, std::vector<BatchSys*> sys, double delt
     }
     launch(h0, false);
     launch(h1, false);
-    for (int k = 0; k < K; ++k)
-      DWF_CHECK_LAUNCH(launch_reduce(part + size_t(k) * pstride, nb, 1, sc + size_t(k) * S_COUNT, S_QQ, 1, s, pend.n));
+    DWF_CHECK_LAUNCH(launch_reduce(part, nb, 1, sc, S_QQ, 1, s, pend.n, K, pstride));
     pend.p[pend.n] = cv(p);
     pend.slot[pend.n] = pend.n;
     ++pend.n;
     launch(h2, true);
     launch(h3, true);
-    for (int k = 0; k < K; ++k)
-      DWF_CHECK_LAUNCH(launch_reduce(part + size_t(k) * pstride, nb, 1, sc + size_t(k) * S_COUNT, S_RRNEW, 0, s));
+    arm_host(ctx, K);
+    DWF_CHECK_LAUNCH(launch_reduce(part, nb, 1, sc, S_RRNEW, 2, s, -1, K, pstride, ctx->h_poll));
     if (pend.n == KX) flush();
-    DWF_CHECK_HIP(hipMemcpyAsync(hsc, sc, sizeof(double) * size_t(K) * S_COUNT, hipMemcpyDeviceToHost, s));
-    DWF_CHECK_HIP(hipStreamSynchronize(s));
+    p_update_ahead();  // (queued before the host reads the residuals, as in cg_normal)
     std::vector<double> rr_new(K), beta(K, 0.0);
     std::vector<int> ru, restart(K, 0), keep(K, 1);
     for (int r2 = 0; r2 < K; ++r2) {
       BatchSys& b = *sys[seg[r2]];
       b.st.iters++;
-      rr_new[r2] = hsc[size_t(r2) * S_COUNT + S_RRNEW];
+      rr_new[r2] = wait_host(ctx, r2);
       if (!std::isfinite(rr_new[r2])) throw Error{DWF_ERR_NAN, "non-finite residual in batched CG"};
       if (MIXED && (rr_new[r2] < delta * delta * b.rr_max || rr_new[r2] <= b.target || rr_new[r2] > 1e4 * b.rr_true))
         ru.push_back(r2);
@@ -797,7 +804,8 @@ static void cg_batched_ilv(dwf_ctx* ctx, std::vector<BatchSys*> sys, double delt
       DWF_CHECK_LAUNCH(launch_zero(xlb, half_bytes<PX>(ns, LT), s));
       upload_tables();
     }
-    p_update(beta);
+    if (leaving || !ru.empty()) p_update(beta);
+    else cur = (cur + 1) % KX;
   }
   if (K > 0) {
     flush();
