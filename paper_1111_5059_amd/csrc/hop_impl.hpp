@@ -47,23 +47,154 @@ inline size_t hop_lds_bytes(const LaunchCfg& cfg, int Ls, bool epi) {
   return b;
 }
 
-// one slice of the per-chirality matrix product along s, from a site's 12 rows in LDS
-template <typename R>
-__device__ __forceinline__ void dense_result(const cx<R>* rows, int stride, int s, int Ls, const R* E, cx<R> o[12]) {
+// The precisions whose dense-epilogue hops hold the gathered sums in registers before the product
+// (asm below) and unroll the product by four slices, at four waves per SIMD.  Left alone, the compiler moves the
+// arithmetic of the gathers behind all of their loads, next to the stores of the sums to LDS: 130 VGPRs
+// instead of 97 at a compile-time extent, 250 with the Moebius prologue (12^3 x 24, Ls = 12, bf16:
+// M_prec 61.6 -> 41.9 us, Moebius 72.6 -> 51.6 us; FP32 63.4 -> 61.4, 16^3 x 32, Ls = 24: 303 -> 291 us).  FP16
+// interleaves the loads by hand and lost 3-10 % with it, FP64 2-10 % at Ls = 24 and 12.
+template <typename P>
+constexpr bool dense_pinned() { return std::is_same<P, P32>::value || std::is_same<P, PB16>::value; }
+
+// one slice of the per-chirality matrix product along s, from a site's 12 rows in LDS (rows 6 to 11
+// off elements further)
+template <typename R, bool PINNED>
+__device__ __forceinline__ void dense_result(const cx<R>* rows, int off, int s, int Ls, const R* E, cx<R> o[12]) {
   const R* E0 = E + s * Ls;
   const R* E1 = E + Ls * Ls + s * Ls;
 #pragma unroll
   for (int k = 0; k < 12; ++k) o[k] = {R(0), R(0)};
-  for (int sp = 0; sp < Ls; ++sp) {
+  auto slice = [&](int sp) {
     const R e0 = E0[sp], e1 = E1[sp];
 #pragma unroll
     for (int k = 0; k < 12; ++k) {
-      const cx<R> v = rows[k * stride + sp];
+      const cx<R> v = rows[(k < 6 ? 0 : off) + k * Ls + sp];
       const R e = k < 6 ? e0 : e1;
       o[k].re = fma(e, v.re, o[k].re);
       o[k].im = fma(e, v.im, o[k].im);
     }
+  };
+  if constexpr (PINNED) {
+    // (one slice at a time waits for its matrix elements: 291 -> 452 us in the FP32 case above)
+#pragma unroll 4
+    for (int sp = 0; sp < Ls; ++sp) slice(sp);
+  } else {
+    for (int sp = 0; sp < Ls; ++sp) slice(sp);
   }
+}
+
+// The site-local products E . psi (fifth_kernel) of a workgroup's sites on the matrix cores, in LDS.  Row
+// (chirality, site, spin-colour of the chirality) holds the Ls slices of one complex component; in rows of
+// 16 and 32 slices (where the matrix cores take them, dense_mfma_shape) the groups of four slices are exchanged by row, so that the operand reads below, four
+// slices of eight rows at once, fall on distinct banks.
+struct DenseRows {
+  int Ls, spb, shift, mask;
+  __device__ DenseRows(int Ls_, int spb_)
+      : Ls(Ls_), spb(spb_), shift(Ls_ == 16 ? 1 : 0), mask(Ls_ == 16 ? 3 : Ls_ == 32 ? 7 : 0) {}
+  __device__ int row(int lsite, int k) const { return k < 6 ? lsite * 6 + k : (spb + lsite) * 6 + k - 6; }
+  __device__ int at(int row, int s) const { return row * Ls + (s ^ (((row >> shift) & mask) << 2)); }
+};
+
+template <typename R>
+struct MfmaTile;
+template <>
+struct MfmaTile<float> {  // lane l: A[l % 16][l / 16], B[l / 16][l % 16], D[4 (l / 16) + r][l % 16]
+  typedef float V __attribute__((ext_vector_type(4)));
+  static __device__ V mma(float a, float b, V c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+  static __device__ int crow(int i) { return i >> 1; }         // complex row and part of operand row i:
+  static __device__ int part(int i) { return i & 1; }          // a lane's results 2 h, 2 h + 1 are one
+  static __device__ int drow(int q, int h) { return 2 * q + h; }  // complex number, of row drow
+};
+template <>
+struct MfmaTile<double> {  // D[l / 16 + 4 r][l % 16]
+  typedef double V __attribute__((ext_vector_type(4)));
+  static __device__ V mma(double a, double b, V c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+  static __device__ int crow(int i) { return (i & 3) + 4 * (i >> 3); }
+  static __device__ int part(int i) { return (i >> 2) & 1; }
+  static __device__ int drow(int q, int h) { return q + 4 * h; }
+};
+
+// The products of all rows, in place, in the type of the arithmetic (FP32 or FP64; the sums come out as those of
+// a chain of fused multiply-adds over the slices): tiles of 8 complex rows (16 real ones) times the
+// transposed matrix, 4 slices per step.  The workgroup has four whole waves (256 / Ls sites, Ls <= 32, rounded
+// up to them); two take each chirality, two tiles at a time.  A tile belongs to one wave, which has read all of it
+// before it writes; rows past the last are read as the last, and what comes of them is not written.
+// One lane per slice, every element of the row read by every lane, was bound by those LDS reads: 16^3 x
+// 32, FP64 Ls = 12 83 -> 56 us, Ls = 24 175 -> 126 us; FP32 Ls = 24 78 -> 68 us, FP16 69 -> 56 us.  In the hops
+// the same product was not faster (FP32 Ls = 16 M_prec 236 -> 243 us, FP64 Ls = 24 542 -> 619 us): the registers it
+// holds across its two barriers cost more than the reads it saves.  Extents beyond 32 would need more
+// accumulators than that: one lane per slice.
+// Where the padding to 4 slices and 16 outputs leaves too little of a tile in use, the lanes' own product
+// is not slower (16^3 x 32, before and after: FP64 Ls = 7 35.4, 35.1, 8 47.8, 36.1, 16 106, 80, 32 220,
+// 160 us; FP32 Ls = 10 23.2, 25.9, 12 28.7, 27.5, 16 36.4, 33.8, 18 42.7, 48.5, 20 54.0, 50.7, 32 159, 100 us;
+// FP16 Ls = 12 28.7, 23.8, 13 27.7, 29.0, 15 32.6, 30.2, 30 85, 73 us).
+template <typename R>
+__device__ __forceinline__ bool dense_mfma_shape(int Ls) {
+  if (sizeof(R) == 8) return Ls >= 8 && Ls <= 32;
+  return Ls == 12 || Ls == 15 || Ls == 16 || (Ls >= 20 && Ls <= 32);
+}
+template <typename R, int KK, int NT>
+__device__ __forceinline__ void dense_tiles(cx<R>* rows, const DenseRows& d, const R* E) {
+  using T = MfmaTile<R>;
+  const int Ls = d.Ls;
+  const int lane = threadIdx.x & 63, w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int i = lane & 15, q = lane >> 4, ch = w & 1;
+  const int nrow = d.spb * 6;
+  R b[NT][KK];
+#pragma unroll
+  for (int jt = 0; jt < NT; ++jt)
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk) {
+      const int j = 16 * jt + i, k = 4 * kk + q;
+      b[jt][kk] = j < Ls && k < Ls ? E[(ch * Ls + j) * Ls + k] : R(0);
+    }
+  __syncthreads();
+#pragma unroll 1
+  for (int t = w >> 1; 8 * t < nrow; t += 4) {
+    R v[2][KK];
+    typename T::V acc[2][NT];
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const int r0 = 8 * (t + 2 * u) + T::crow(i);
+      const int row = ch * nrow + (r0 < nrow ? r0 : nrow - 1);
+      const R* p = reinterpret_cast<const R*>(rows + row * Ls) + T::part(i);
+      const int x = ((row >> d.shift) & d.mask) << 2;
+#pragma unroll
+      for (int kk = 0; kk < KK; ++kk) {
+        const int s = 4 * kk + q;
+        v[u][kk] = p[2 * ((s < Ls ? s : Ls - 1) ^ x)];
+        if (s >= Ls) v[u][kk] = R(0);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int jt = 0; jt < NT; ++jt) acc[u][jt] = typename T::V{R(0), R(0), R(0), R(0)};
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int jt = 0; jt < NT; ++jt) acc[u][jt] = T::mma(v[u][kk], b[jt][kk], acc[u][jt]);
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+#pragma unroll
+      for (int jt = 0; jt < NT; ++jt)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          const int r = 8 * (t + 2 * u) + T::drow(q, h), s = 16 * jt + i;
+          if (r < nrow && s < Ls) rows[d.at(ch * nrow + r, s)] = {acc[u][jt][2 * h], acc[u][jt][2 * h + 1]};
+        }
+  }
+  __syncthreads();
+}
+
+template <typename R>
+__device__ __forceinline__ void dense_mfma(cx<R>* rows, const DenseRows& d, const R* E) {
+  if (d.Ls <= 12) dense_tiles<R, 3, 1>(rows, d, E);
+  else if (d.Ls <= 16) dense_tiles<R, 4, 1>(rows, d, E);
+  else if (d.Ls <= 24) dense_tiles<R, 6, 2>(rows, d, E);
+  else dense_tiles<R, 8, 2>(rows, d, E);
 }
 
 // Moebius prologue of one slice s: the hop's input becomes b_s psi_s + u P+ psi_{s-1} +
@@ -414,7 +545,12 @@ __device__ __forceinline__ void hop_dir(const HopArgs<P>& a, const int* nb, cons
 // kernel is bound by the latency of its gathers; 4 for the fused CG step without an epilogue
 // matrix, which would spill at 5.  Several slices per thread keep the default.
 template <typename P, int NS, int EPI, bool CG>
-constexpr int hop_min_waves() { return std::is_same<P, P16>::value && NS == 1 ? (CG && EPI == 0 ? 4 : 5) : 1; }
+constexpr int hop_min_waves() {
+  if (NS != 1) return 1;
+  if (std::is_same<P, P16>::value) return CG && EPI == 0 ? 4 : 5;
+  if (EPI == 1 && dense_pinned<P>()) return 4;
+  return 1;
+}
 
 // ST: neighbour spinors staged through LDS (FP16, compile-time Ls, one slice per lane, no
 // prologue, spb = 256 / Ls); its links are staged too (LL), so that the direction loop issues
@@ -651,6 +787,12 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
       hop_dir<PAIRS ? 3 : 6, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
       hop_dir<7, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
     }
+    if constexpr (EPI == 1 && dense_pinned<P>()) {
+#pragma unroll
+      for (int j = 0; j < NS; ++j)
+#pragma unroll
+        for (int k = 0; k < 12; ++k) asm volatile("" : "+v"(acc[j][k].re), "+v"(acc[j][k].im));
+    }
   }
   if constexpr (!std::is_same<P, P16>::value) {  // (the FP16 path folds the scale into the norm)
 #pragma unroll
@@ -687,28 +829,8 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
     if (active) {
 #pragma unroll
       for (int j = 0; j < NS; ++j) {
-        const int s = s0 + j * tps;
-        const R* E0 = a.E + s * Ls;
-        const R* E1 = a.E + Ls * Ls + s * Ls;
         cx<R> o[12];
-#pragma unroll
-        for (int k = 0; k < 12; ++k) o[k] = {R(0), R(0)};
-        const cx<R>* row = lds + lsite * 12 * Ls;
-        for (int sp = 0; sp < Ls; ++sp) {
-          const R e0 = E0[sp], e1 = E1[sp];
-#pragma unroll
-          for (int k = 0; k < 6; ++k) {
-            const cx<R> v = row[k * Ls + sp];
-            o[k].re = fma(e0, v.re, o[k].re);
-            o[k].im = fma(e0, v.im, o[k].im);
-          }
-#pragma unroll
-          for (int k = 6; k < 12; ++k) {
-            const cx<R> v = row[k * Ls + sp];
-            o[k].re = fma(e1, v.re, o[k].re);
-            o[k].im = fma(e1, v.im, o[k].im);
-          }
-        }
+        dense_result<R, dense_pinned<P>()>(lds + lsite * 12 * Ls, 0, s0 + j * tps, Ls, a.E, o);
 #pragma unroll
         for (int k = 0; k < 12; ++k) acc[j][k] = o[k];
       }
@@ -926,7 +1048,7 @@ __device__ __forceinline__ void hop_split_body(const HopArgs<P>& a, long bid, in
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    if (active) dense_result<R>(rows, Ls, s, Ls, a.E, acc[0]);
+    if (active) dense_result<R, false>(rows, 0, s, Ls, a.E, acc[0]);
   }
   constexpr bool XS = CG && !std::is_same<P, P64>::value && (LS == 8 || LS == 16 || LS == 32);
   double nrm = 0.0;
@@ -1245,9 +1367,9 @@ int launch_hop_eo5(const HopArgs<P>& a0, const HopArgs<P>& a1, bool dagger, cons
 
 // ------------------------------------------------------------------ site-local fifth-dimension matrices
 template <typename P, int LSEG>
-__global__ void __launch_bounds__(256) fifth_kernel(CHalf<P> in, Half<P> out, const typename P::R* E,
-                                                     FifthScan<typename P::R> es, CHalf<P> xin, typename P::R ax,
-                                                     long nsites, int Ls_rt, int spb, double* norm_partials) {
+__global__ void __launch_bounds__(256, (LSEG == 0 && sizeof(typename P::R) == 4 ? 6 : 1))
+    fifth_kernel(CHalf<P> in, Half<P> out, const typename P::R* E, FifthScan<typename P::R> es, CHalf<P> xin,
+                 typename P::R ax, long nsites, int Ls_rt, int spb, double* norm_partials) {
   using R = typename P::R;
   extern __shared__ __align__(16) unsigned char smem_raw[];
   __shared__ double red[16];
@@ -1285,33 +1407,24 @@ __global__ void __launch_bounds__(256) fifth_kernel(CHalf<P> in, Half<P> out, co
     }
     return;
   }
+  const DenseRows d(Ls, spb);
+  const bool mfma = dense_mfma_shape<R>(Ls);
   if (active) {
     cx<R> v[12];
     load_spinor<P>(in, x, s, Ls, v);
 #pragma unroll
-    for (int k = 0; k < 12; ++k) lds[(lsite * 12 + k) * Ls + s] = v[k];
+    for (int k = 0; k < 12; ++k) lds[d.at(d.row(lsite, k), s)] = v[k];
   }
-  __syncthreads();
+  if (mfma) dense_mfma<R>(lds, d, E);
+  else __syncthreads();
   double nrm = 0.0;
   if (active) {
     cx<R> o[12];
+    if (mfma) {
 #pragma unroll
-    for (int k = 0; k < 12; ++k) o[k] = {R(0), R(0)};
-    const R* E0 = E + s * Ls;
-    const R* E1 = E + Ls * Ls + s * Ls;
-    const cx<R>* row = lds + lsite * 12 * Ls;
-    for (int sp = 0; sp < Ls; ++sp) {
-      const R e0 = E0[sp], e1 = E1[sp];
-#pragma unroll
-      for (int k = 0; k < 6; ++k) {
-        o[k].re = fma(e0, row[k * Ls + sp].re, o[k].re);
-        o[k].im = fma(e0, row[k * Ls + sp].im, o[k].im);
-      }
-#pragma unroll
-      for (int k = 6; k < 12; ++k) {
-        o[k].re = fma(e1, row[k * Ls + sp].re, o[k].re);
-        o[k].im = fma(e1, row[k * Ls + sp].im, o[k].im);
-      }
+      for (int k = 0; k < 12; ++k) o[k] = lds[d.at(d.row(lsite, k), s)];
+    } else {
+      dense_result<R, true>(lds + d.row(lsite, 0) * Ls, (spb - 1) * 6 * Ls, s, Ls, E, o);
     }
     if (xin.data) {
       cx<R> xv[12];
@@ -1359,8 +1472,9 @@ int launch_fifth(CHalf<P> in, Half<P> out, const typename P::R* E, const FifthSc
   const long blocks = (nsites + spb - 1) / spb;
   const size_t lds = size_t(spb) * 12 * Ls * sizeof(cx<R>);
   FifthScan<R> e{};
-  hipLaunchKernelGGL((fifth_kernel<P, 0>), dim3((unsigned)blocks), dim3(spb * Ls), lds, st, in, out, E, e, x, ax, nsites,
-                     Ls, spb, norm_partials);
+  // (whole waves: the matrix cores work on the registers of all 64 lanes)
+  hipLaunchKernelGGL((fifth_kernel<P, 0>), dim3((unsigned)blocks), dim3((spb * Ls + 63) & ~63), lds, st, in, out, E, e, x,
+                     ax, nsites, Ls, spb, norm_partials);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 

@@ -98,3 +98,61 @@ def test_full_field_tiles(env, Ls, prec):
         assert torch.equal(full, torch.cat(halves))
         both = lat.unpack(halves[0], dwf.KIND_EVEN, P) + lat.unpack(halves[1], dwf.KIND_ODD, P)
         assert torch.equal(lat.unpack(full, dwf.KIND_FULL, P), both)
+
+
+@pytest.mark.parametrize("Ls", [2, 3, 8, 9, 12, 13, 16, 17, 24, 31, 32, 33])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16", "bf16"])
+def test_site_local_dense_products(env, ora, Ls, prec):
+    """A^-1 and A^-dag with coefficients per slice (no recurrence at any extent): the matrix-core tiles
+    at the edges of their extents (steps of 4 slices, 16 output slices, rows of 16 and 32 exchanged), the
+    last one-lane-per-slice extent, and fewer sites than one workgroup or a part of a second one."""
+    dwf, ctx = env
+    P = dwf.PREC_NAMES[prec]
+    w = 1.5 + 0.5 * np.sin(np.arange(Ls))
+    b_s, c_s = (w + 1) / 2, (w - 1) / 2
+    for dims in ((2, 2, 2, 2), (4, 6, 2, 6)):
+        psi = mask(synth.gaussian_spinor(dims, Ls, 890 + Ls), dims, 0)
+        lat = dwf.Lattice(ctx, dims, Ls, mass=0.3, b_s=b_s, c_s=c_s)
+        po = ora.params(dims, Ls, mass=0.3, bs=b_s, cs=c_s)
+        U = lat.pack_gauge(synth.random_links(dims, 0.5, 891), P)
+        src = lat.pack(psi, dwf.KIND_EVEN, P)
+        for dag in (False, True):
+            dst = lat.empty(dwf.KIND_EVEN, P)
+            dwf.mobius_dslash(ctx, lat.params(P), U, src, dst, dwf.OP_AINV, 0, dag)
+            ref = mask(ora.fifth(po, psi, "Ainv" + ("dag" if dag else "")), dims, 0)
+            err = rel_err(lat.unpack_np(dst, dwf.KIND_EVEN, P), ref)
+            assert err < PREC_TOL[prec], (dims, dag, err)
+
+
+@pytest.mark.parametrize("dims,Ls", [((2, 2, 2, 2), 2), ((4, 2, 6, 2), 7), ((2, 4, 2, 6), 12), ((2, 2, 6, 2), 16),
+                                     ((2, 4, 2, 2), 32), ((2, 2, 2, 4), 63), ((2, 2, 2, 4), 64), ((2, 2, 2, 4), 65),
+                                     ((8, 8, 8, 8), 16), ((8, 8, 8, 12), 16), ((8, 8, 8, 16), 16), ((8, 8, 8, 12), 17)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16", "bf16"])
+@pytest.mark.parametrize("b,c", [(1.0, 0.0), (1.5, 0.5)])
+def test_small_field_hop(env, dims, Ls, prec, b, c):
+    """Hop, M_prec and adjoints of fields below the size at which the directions stop being spread over
+    the waves (32768 5D sites in 16 bit, 49152 in FP64, 65536 in FP32; extents to 64), at the
+    limits and beyond: the default shape against an explicit one, which takes the general kernel."""
+    dwf, ctx = env
+    P = dwf.PREC_NAMES[prec]
+    lat = dwf.Lattice(ctx, dims, Ls, mass=0.2, b=b, c=c, tbc=1)
+    Ug, p = lat.pack_gauge(synth.random_links(dims, 0.5, 900), P), lat.params(P)
+    src = lat.pack(synth.gaussian_spinor(dims, Ls, 901 + Ls), dwf.KIND_ODD, P)
+
+    def results():
+        out = []
+        for op, par, kind in ((dwf.OP_HOP, 0, dwf.KIND_EVEN), (dwf.OP_MPREC, 1, dwf.KIND_ODD)):
+            for dag in (False, True):
+                dst = lat.empty(kind, P)
+                dwf.mobius_dslash(ctx, p, Ug, src, dst, op, par, dag)
+                out.append(lat.unpack_np(dst, kind, P))
+        return out
+
+    default = results()
+    dwf.dwf_tune_set(ctx, P, Ls, min(16, max(1, 128 // Ls)), 1)
+    try:
+        explicit = results()
+    finally:
+        dwf.dwf_tune_set(ctx, P, Ls, 0, 0)
+    for i, (a, e) in enumerate(zip(default, explicit)):
+        assert rel_err(a, e) < PREC_TOL[prec], i
