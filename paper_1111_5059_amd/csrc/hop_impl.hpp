@@ -543,11 +543,15 @@ __device__ __forceinline__ void hop_dir(const HopArgs<P>& a, const int* nb, cons
 
 // FP16 with one slice per thread: at least 5 waves per SIMD (at most 102 VGPRs), since the
 // kernel is bound by the latency of its gathers; 4 for the fused CG step without an epilogue
-// matrix, which would spill at 5.  Several slices per thread keep the default.
-template <typename P, int NS, int EPI, bool CG>
+// matrix, which would spill at 5.  3 with the Moebius prologue at a run-time extent, which spills 350
+// bytes a lane at 5 and 130 at 4 (16^3 x 32, Ls = 24: M_prec 1232 -> 255 us, Ls = 10 529 -> 155 us), and
+// without an epilogue (Ls = 8, 12, 16, 32: 85, 110, 134, 253 us at 5 and at 4, 69, 72, 81, 131 us at 3); the
+// other compile-time extents spill 12 to 70 bytes at 5 and none at 3, and take 180 and 185 us (Ls = 16) and 157
+// and 176 us (Ls = 12).  Several slices per thread keep the default.
+template <typename P, int LS, int NS, bool PRO, int EPI, bool CG>
 constexpr int hop_min_waves() {
   if (NS != 1) return 1;
-  if (std::is_same<P, P16>::value) return CG && EPI == 0 ? 4 : 5;
+  if (std::is_same<P, P16>::value) return PRO && (LS == 0 || EPI == 0) ? 3 : CG && EPI == 0 ? 4 : 5;
   if (EPI == 1 && dense_pinned<P>()) return 4;
   return 1;
 }
@@ -1098,7 +1102,7 @@ __global__ void __launch_bounds__(256) hop_kernel(HopArgs<P> a, int spb) {
 }
 
 template <typename P, int LS, int NS, bool DAG, bool PRO, int EPI, bool LL, bool CG, bool ST>
-__global__ void __launch_bounds__(256, (hop_min_waves<P, NS, EPI, CG>())) hop_kernel(HopArgs<P> a, int spb, int xcd) {
+__global__ void __launch_bounds__(256, (hop_min_waves<P, LS, NS, PRO, EPI, CG>())) hop_kernel(HopArgs<P> a, int spb, int xcd) {
   const long bid = xcd ? xcd_block(blockIdx.x, gridDim.x) : (long)blockIdx.x;
   hop_body<P, LS, NS, DAG, PRO, EPI, LL, CG, ST>(a, bid, blockIdx.x, spb);
 }
@@ -1110,7 +1114,7 @@ __global__ void __launch_bounds__(256, (hop_min_waves<P, NS, EPI, CG>())) hop_ke
 // fields' arguments (the same kernel variant for all of them); each field's norm partials are
 // indexed by its site block.
 template <typename P, int LS, int NS, bool DAG, bool PRO, int EPI, bool LL, bool CG, bool ST>
-__global__ void __launch_bounds__(256, (hop_min_waves<P, NS, EPI, CG>()))
+__global__ void __launch_bounds__(256, (hop_min_waves<P, LS, NS, PRO, EPI, CG>()))
     hop_batch_kernel(const HopArgs<P>* __restrict__ args, int nrhs, int spb, int xcd) {
   const long b = xcd ? xcd_block(blockIdx.x, gridDim.x) : (long)blockIdx.x;
   const long bid = b / nrhs;
@@ -1120,7 +1124,7 @@ __global__ void __launch_bounds__(256, (hop_min_waves<P, NS, EPI, CG>()))
 // Right-hand sides interleaved along the fifth dimension (segments of RS slices, a.Ls = their
 // number times RS; no Moebius prologue): one slice per lane, the site's a.Ls lanes contiguous.
 template <typename P, bool DAG, int EPI, bool LL, bool CG, int RS>
-__global__ void __launch_bounds__(256, (hop_min_waves<P, 1, EPI, CG>())) hop_ilv_kernel(HopArgs<P> a, int spb, int xcd) {
+__global__ void __launch_bounds__(256, (hop_min_waves<P, 0, 1, false, EPI, CG>())) hop_ilv_kernel(HopArgs<P> a, int spb, int xcd) {
   const long bid = xcd ? xcd_block(blockIdx.x, gridDim.x) : (long)blockIdx.x;
   hop_body<P, 0, 1, DAG, false, EPI, LL, CG, false, RS>(a, bid, blockIdx.x, spb);
 }
