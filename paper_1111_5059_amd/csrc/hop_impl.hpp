@@ -85,8 +85,9 @@ __device__ __forceinline__ void dense_result(const cx<R>* rows, int off, int s, 
 
 // The site-local products E . psi (fifth_kernel) of a workgroup's sites on the matrix cores, in LDS.  Row
 // (chirality, site, spin-colour of the chirality) holds the Ls slices of one complex component; in rows of
-// 16 and 32 slices (where the matrix cores take them, dense_mfma_shape) the groups of four slices are exchanged by row, so that the operand reads below, four
-// slices of eight rows at once, fall on distinct banks.
+// 16 and 32 slices (the matrix cores take all of those, dense_mfma_shape) the groups of four slices are
+// exchanged by row, so that the operand reads below, four slices of eight rows at once, fall on distinct
+// banks.
 struct DenseRows {
   int Ls, spb, shift, mask;
   __device__ DenseRows(int Ls_, int spb_)
