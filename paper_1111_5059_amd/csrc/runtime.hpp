@@ -341,12 +341,18 @@ struct Op {
   // M_prec psi = psi - 1/4 A^-1 H_oe (F A^-1) H_eo F psi    (odd -> odd); tmp_f (optional, Moebius):
   // room for F psi (see input_factor);
   // ainvdag_out (optional, see second_output_ok): also A^-dag (M_prec psi); with it, out may be
-  // empty (the norm partials and A^-dag (M_prec psi) only)
+  // empty (the norm partials and A^-dag (M_prec psi) only).
+  // The second factor F is part of the first hop's epilogue, so that the second hop runs without the
+  // prologue and the even field stored in between is F A^-1 (...).  In bf16 it is A^-1 (...), and the
+  // second hop applies F: F enlarges the rounding of the stored field less than its components, and with
+  // F A^-1 stored the result was 1.2-1.6 % further from the exact one (in FP16, whose prologue itself
+  // works in FP16, 7 % nearer; FP32 rounds no more often either way).
   void mprec(CHalf<P> in, Half<P> out, Half<P> tmp_e, double* partials = nullptr,
              Half<P> ainvdag_out = {nullptr, nullptr}, Half<P> tmp_f = {nullptr, nullptr}) const {
+    constexpr bool FOLD = P::ID != DWF_BF16;
     const bool f = input_factor(in, tmp_f);
-    hop(0, f ? cv(tmp_f) : in, tmp_e, false, !f, 1.0, em(moebius ? E_F_AINV : E_AINV));
-    hop(1, cv(tmp_e), out, false, false, -0.25, em(E_AINV), in, 1.0, partials, CgStep(), ainvdag_out, E_AINVDAG);
+    hop(0, f ? cv(tmp_f) : in, tmp_e, false, !f, 1.0, em(moebius && FOLD ? E_F_AINV : E_AINV));
+    hop(1, cv(tmp_e), out, false, !FOLD, -0.25, em(E_AINV), in, 1.0, partials, CgStep(), ainvdag_out, E_AINVDAG);
   }
   // M_prec psi from fpsi = F psi prepared by the caller (the CG p update): both hops without
   // the input factor, the first with the epilogue F A^-1 (Moebius operators)

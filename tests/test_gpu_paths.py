@@ -156,3 +156,47 @@ def test_small_field_hop(env, dims, Ls, prec, b, c):
         dwf.dwf_tune_set(ctx, P, Ls, 0, 0)
     for i, (a, e) in enumerate(zip(default, explicit)):
         assert rel_err(a, e) < PREC_TOL[prec], i
+
+
+def bf16_rounded(a):
+    """complex128 with both parts rounded to bf16"""
+    import torch
+    t = torch.from_numpy(np.ascontiguousarray(a).view(np.float64)).to(torch.bfloat16).to(torch.float64)
+    return t.numpy().view(np.complex128)
+
+
+@pytest.mark.parametrize("Ls", [8, 12, 16])
+@pytest.mark.parametrize("kind", ["moebius", "sdep"])
+@pytest.mark.parametrize("shape", ["default", "explicit"])
+def test_bf16_moebius_stores_the_even_field_before_the_input_factor(env, ora, Ls, kind, shape):
+    """M_prec in bf16 stores A^-1 H F psi on the even sites, and its second hop applies F.  On inputs of
+    bf16 values the result is, up to FP32 arithmetic, the FP64 composition with that field rounded to
+    bf16, rounded once more: an FP32 sum falls on the other side of a rounding boundary (relative error
+    of a few 2^-24 against a spacing of 2^-8) once in some 10^4 components, and each of the about 10^3
+    even components an output depends on moves it by a tenth of its spacing or less, so that about one
+    output in a hundred may differ.  A field stored after F has other roundings in every component."""
+    dwf, ctx = env
+    dims = (4, 4, 2, 6)
+    kw, okw = {"b": 1.5, "c": 0.5}, {"b": 1.5, "c": 0.5}
+    if kind == "sdep":
+        w = 1.5 + 0.5 * np.sin(np.arange(Ls))
+        kw = {"b_s": (w + 1) / 2, "c_s": (w - 1) / 2}
+        okw = {"bs": kw["b_s"], "cs": kw["c_s"]}
+    U = bf16_rounded(synth.random_links(dims, 0.5, 910))
+    psi = bf16_rounded(mask(synth.gaussian_spinor(dims, Ls, 911 + Ls), dims, 1))
+    lat = dwf.Lattice(ctx, dims, Ls, mass=0.2, tbc=1, **kw)
+    po = ora.params(dims, Ls, mass=0.2, tbc=1, **okw)
+    Ug, p = lat.pack_gauge(U, dwf.BF16), lat.params(dwf.BF16)
+    src, out = lat.pack(psi, dwf.KIND_ODD, dwf.BF16), lat.empty(dwf.KIND_ODD, dwf.BF16)
+    if shape == "explicit":
+        dwf.dwf_tune_set(ctx, dwf.BF16, Ls, 128 // Ls, 1)
+    try:
+        dwf.mobius_dslash(ctx, p, Ug, src, out, dwf.OP_MPREC, 1, False)
+    finally:
+        dwf.dwf_tune_set(ctx, dwf.BF16, Ls, 0, 0)
+    got = lat.unpack_np(out, dwf.KIND_ODD, dwf.BF16)
+    even = ora.fifth(po, ora.hop5(po, U, ora.fifth(po, psi, "F"), out_parity=0), "Ainv")
+    second = ora.hop5(po, U, ora.fifth(po, bf16_rounded(even), "F"), out_parity=1)
+    ref = psi - 0.25 * mask(ora.fifth(po, second, "Ainv"), dims, 1)
+    other = (got != bf16_rounded(ref))[mask(np.ones_like(psi), dims, 1) != 0]
+    assert other.mean() < 0.05
