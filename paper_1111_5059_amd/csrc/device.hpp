@@ -297,20 +297,22 @@ struct FifthScan {
 // Site-local operators along s on the 12 components held by this lane (slice s) when the LSEG
 // lanes of a site are the consecutive lanes [seg LSEG, (seg + 1) LSEG) of one wave.
 //
-// The inverse of (alpha + beta S_d) is that of (1 - a S_d), times 1/alpha.  With the cyclic
-// boundary S_d^LSEG = -m it is exactly
-//   (1 - a S)^-1 = (1 + a S)(1 + a^2 S^2)(1 + a^4 S^4) ... / (1 + m a^LSEG):
-// log2 LSEG steps v += c v_{s -+ off}, each a rotation of the segment with the per-lane
-// coefficient c = a^off, or -m a^off where the rotation wraps.  In FP32 a segment of 16 lanes
-// is one DPP row, and a step is one v_fmac_f32 with a rotated operand per value: no LDS-pipe
-// traffic, no selects and no separate pass for the boundary.  A segment of 32 lanes is two rows:
-// a scan with zero start inside each row (row shifts that read 0 beyond the row), then the two
-// rows' carries, which only need the rows' last (first) values, in closed form.  Other segments
-// and FP64 rotate with ds_bpermute (one rotation and one fma per step and value).
-// What it replaced, a zero-start scan with a select per step and a separate boundary pass, cost
-// 144 ds_bpermute and about 340 VALU instructions per lane.  The FP16 hops with this epilogue at
-// 24^3 x 64, Ls = 32 went from 676 to 599 us, those with two of them from 920 to 752 us; FP32,
-// Ls = 16: 615 to 570 and 725 to 640 us.
+// The inverse of (alpha + beta S_d) is the recurrence y_s = u_s + a y_{s-+1}, u = w / alpha: a scan over
+// the segment with zero start, log2 LSEG steps v_s += a^off v_{s -+ off}, then the cyclic boundary
+// y_{-1} = -m y_{LSEG-1} (resp. y_LSEG = -m y_0) in closed form:
+//   y_s = P_s - m a^{s+1} P_{LSEG-1} / (1 + m a^LSEG)  or  y_s = Q_s - m a^{LSEG-s} Q_0 / (1 + m a^LSEG).
+// In FP32 a segment of 16 lanes is one DPP row: a step is one v_fmac_f32 whose shifted operand is 0
+// beyond the row, and the boundary one with the row's last (first) value.  A segment of 32 lanes is two
+// rows: the scan inside each row, then the two rows' carries, which only need the rows' last (first)
+// values, in closed form.  Two segments of 8 lanes share a row.  FP64 moves both words of a value with DPP
+// (32 lanes: with ds_bpermute) and multiplies and adds them.
+// Moving every value with ds_bpermute and selecting took 144 of them and about 340 VALU instructions per
+// lane in FP32: the FP16 hops with this epilogue at 24^3 x 64, Ls = 32 went from 676 to 599 us, those with
+// two of them from 920 to 752 us; M_prec in FP64, Ls = 16 at 16^3 x 32 340 -> 297 us (DPP and the rest of that
+// hop's changes), A^-1 in FP32, Ls = 8 at 12^3 x 24 7.7 -> 5.7 us.
+// Rotations with the boundary's factor -m in the wrapped lanes need no closing step, but round every
+// lane in every step and the common factor 1 / (1 + m a^LSEG) once more: FP32 A^-1 at Ls = 8 was 1.38 times as
+// far from the exact result, at Ls = 16 1.04 times.
 // (The fmac steps are inline asm because the compiler emits a DPP move and a separate fma.  Each
 // block starts with the five wait states that DPP needs after an EXEC or operand write; inside a
 // block a value is read again only twelve instructions after it was written.)
@@ -319,36 +321,68 @@ __device__ __forceinline__ R seg_shfl(R v, int src) {
   return __shfl(v, src, LSEG);
 }
 
-#define DWF_DPP12(CTRL, COEF)                                                                      \
-  "v_fmac_f32_dpp %0, %0, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
-  "v_fmac_f32_dpp %1, %1, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
-  "v_fmac_f32_dpp %2, %2, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
-  "v_fmac_f32_dpp %3, %3, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
-  "v_fmac_f32_dpp %4, %4, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
-  "v_fmac_f32_dpp %5, %5, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
-  "v_fmac_f32_dpp %6, %6, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
-  "v_fmac_f32_dpp %7, %7, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
-  "v_fmac_f32_dpp %8, %8, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
-  "v_fmac_f32_dpp %9, %9, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"             \
-  "v_fmac_f32_dpp %10, %10, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"           \
-  "v_fmac_f32_dpp %11, %11, " COEF " " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"
-#define DWF_DPP_SCAN(C1, C2, C4, C8)                                                               \
-  asm("s_nop 4\n" DWF_DPP12(C1, "%12") DWF_DPP12(C2, "%13") DWF_DPP12(C4, "%14") DWF_DPP12(C8, "%15") \
+#define DWF_DPP12_BANKS(CTRL, COEF, BANKS)                                                          \
+  "v_fmac_f32_dpp %0, %0, " COEF " " CTRL " row_mask:0xf bank_mask:" BANKS " bound_ctrl:1\n"        \
+  "v_fmac_f32_dpp %1, %1, " COEF " " CTRL " row_mask:0xf bank_mask:" BANKS " bound_ctrl:1\n"        \
+  "v_fmac_f32_dpp %2, %2, " COEF " " CTRL " row_mask:0xf bank_mask:" BANKS " bound_ctrl:1\n"        \
+  "v_fmac_f32_dpp %3, %3, " COEF " " CTRL " row_mask:0xf bank_mask:" BANKS " bound_ctrl:1\n"        \
+  "v_fmac_f32_dpp %4, %4, " COEF " " CTRL " row_mask:0xf bank_mask:" BANKS " bound_ctrl:1\n"        \
+  "v_fmac_f32_dpp %5, %5, " COEF " " CTRL " row_mask:0xf bank_mask:" BANKS " bound_ctrl:1\n"        \
+  "v_fmac_f32_dpp %6, %6, " COEF " " CTRL " row_mask:0xf bank_mask:" BANKS " bound_ctrl:1\n"        \
+  "v_fmac_f32_dpp %7, %7, " COEF " " CTRL " row_mask:0xf bank_mask:" BANKS " bound_ctrl:1\n"        \
+  "v_fmac_f32_dpp %8, %8, " COEF " " CTRL " row_mask:0xf bank_mask:" BANKS " bound_ctrl:1\n"        \
+  "v_fmac_f32_dpp %9, %9, " COEF " " CTRL " row_mask:0xf bank_mask:" BANKS " bound_ctrl:1\n"        \
+  "v_fmac_f32_dpp %10, %10, " COEF " " CTRL " row_mask:0xf bank_mask:" BANKS " bound_ctrl:1\n"      \
+  "v_fmac_f32_dpp %11, %11, " COEF " " CTRL " row_mask:0xf bank_mask:" BANKS " bound_ctrl:1\n"
+#define DWF_DPP12(CTRL, COEF) DWF_DPP12_BANKS(CTRL, COEF, "0xf")
+#define DWF_DPP_STEPS(STEPS, ...)                                                                  \
+  asm("s_nop 4\n" STEPS                                                                            \
       : "+v"(v[0].re), "+v"(v[0].im), "+v"(v[1].re), "+v"(v[1].im), "+v"(v[2].re), "+v"(v[2].im), "+v"(v[3].re), \
         "+v"(v[3].im), "+v"(v[4].re), "+v"(v[4].im), "+v"(v[5].re), "+v"(v[5].im)                  \
-      : "v"(c1), "v"(c2), "v"(c4), "v"(c8))
+      : __VA_ARGS__)
+#define DWF_DPP_SCAN(SH)                                                                           \
+  DWF_DPP12(SH ":1", "%12") DWF_DPP12(SH ":2", "%13") DWF_DPP12(SH ":4", "%14") DWF_DPP12(SH ":8", "%15")
 
-// four steps on six components: rotations of the 16-lane row (from s - off, BACK from s + off),
-// or shifts that read 0 beyond it
+// the four steps of the scan on six components in a 16-lane row (from s - off, BACK from s + off; 0
+// beyond the row)
 template <bool BACK>
-__device__ __forceinline__ void row_rotate_steps(cx<float>* v, float c1, float c2, float c4, float c8) {
-  if constexpr (BACK) DWF_DPP_SCAN("row_ror:15", "row_ror:14", "row_ror:12", "row_ror:8");
-  else DWF_DPP_SCAN("row_ror:1", "row_ror:2", "row_ror:4", "row_ror:8");
+__device__ __forceinline__ void row_scan(cx<float>* v, float c1, float c2, float c4, float c8) {
+  if constexpr (BACK) DWF_DPP_STEPS(DWF_DPP_SCAN("row_shl"), "v"(c1), "v"(c2), "v"(c4), "v"(c8));
+  else DWF_DPP_STEPS(DWF_DPP_SCAN("row_shr"), "v"(c1), "v"(c2), "v"(c4), "v"(c8));
 }
+// ... and w times the row's last (BACK first) value added
 template <bool BACK>
-__device__ __forceinline__ void row_shift_steps(cx<float>* v, float c1, float c2, float c4, float c8) {
-  if constexpr (BACK) DWF_DPP_SCAN("row_shl:1", "row_shl:2", "row_shl:4", "row_shl:8");
-  else DWF_DPP_SCAN("row_shr:1", "row_shr:2", "row_shr:4", "row_shr:8");
+__device__ __forceinline__ void row_scan_close(cx<float>* v, float c1, float c2, float c4, float c8, float w) {
+  if constexpr (BACK)
+    DWF_DPP_STEPS(DWF_DPP_SCAN("row_shl") DWF_DPP12("row_newbcast:0", "%16"), "v"(c1), "v"(c2), "v"(c4), "v"(c8), "v"(w));
+  else
+    DWF_DPP_STEPS(DWF_DPP_SCAN("row_shr") DWF_DPP12("row_newbcast:15", "%16"), "v"(c1), "v"(c2), "v"(c4), "v"(c8), "v"(w));
+}
+// The same in segments of 8 lanes, two to a row: in the steps of 1 and 2 the lanes whose source lies in
+// the other segment (vcc) take 0 (never a product with its value, which may be infinite); the step of 4
+// and the boundary's values fall into whole banks of four lanes.
+#define DWF_MASKED(K, CTRL, COEF)                                                                  \
+  "v_cndmask_b32_dpp %12, %" #K ", %13, vcc " CTRL " row_mask:0xf bank_mask:0xf bound_ctrl:1\n"    \
+  "v_fmac_f32 %" #K ", " COEF ", %12\n"
+#define DWF_MASKED12(CTRL, COEF)                                                                   \
+  DWF_MASKED(0, CTRL, COEF) DWF_MASKED(1, CTRL, COEF) DWF_MASKED(2, CTRL, COEF) DWF_MASKED(3, CTRL, COEF)    \
+  DWF_MASKED(4, CTRL, COEF) DWF_MASKED(5, CTRL, COEF) DWF_MASKED(6, CTRL, COEF) DWF_MASKED(7, CTRL, COEF)    \
+  DWF_MASKED(8, CTRL, COEF) DWF_MASKED(9, CTRL, COEF) DWF_MASKED(10, CTRL, COEF) DWF_MASKED(11, CTRL, COEF)
+#define DWF_HALF_ROW(SH, BANKS4, LOW, HIGH)                                                        \
+  asm("s_mov_b64 vcc, %18\ns_nop 4\n" DWF_MASKED12(SH ":1", "%14") "s_mov_b64 vcc, %19\n"         \
+      DWF_MASKED12(SH ":2", "%15") DWF_DPP12_BANKS(SH ":4", "%16", BANKS4)                         \
+      DWF_DPP12_BANKS("row_newbcast:" LOW, "%17", "0x3") DWF_DPP12_BANKS("row_newbcast:" HIGH, "%17", "0xc") \
+      : "+v"(v[0].re), "+v"(v[0].im), "+v"(v[1].re), "+v"(v[1].im), "+v"(v[2].re), "+v"(v[2].im), "+v"(v[3].re), \
+        "+v"(v[3].im), "+v"(v[4].re), "+v"(v[4].im), "+v"(v[5].re), "+v"(v[5].im), "=&v"(t)        \
+      : "v"(0.0f), "v"(c1), "v"(c2), "v"(c4), "v"(w), "s"(out1), "s"(out2)                         \
+      : "vcc")
+template <bool BACK>
+__device__ __forceinline__ void half_row_scan_close(cx<float>* v, float c1, float c2, float c4, float w) {
+  float t;
+  const uint64_t out1 = BACK ? 0x8080808080808080ULL : 0x0101010101010101ULL;
+  const uint64_t out2 = BACK ? 0xc0c0c0c0c0c0c0c0ULL : 0x0303030303030303ULL;
+  if constexpr (BACK) DWF_HALF_ROW("row_shl", "0x5", "0", "8");
+  else DWF_HALF_ROW("row_shr", "0xa", "7", "15");
 }
 // the value of lane LANE of this lane's group of 32
 template <int LANE>
@@ -356,17 +390,77 @@ __device__ __forceinline__ float bcast32(float v) {
   return __builtin_bit_cast(float, __builtin_amdgcn_ds_swizzle(__builtin_bit_cast(int, v), LANE << 5));
 }
 
-// (1 - a S_d)^-1 (1 + m a^LSEG) on six components (32 lanes: (1 - a S_d)^-1)
+// one DPP move within a 16-lane row; lanes whose source lies beyond the row get 0, lanes of the banks (groups
+// of four) outside BANKS keep old
+template <int CTRL, int BANKS = 0xf>
+__device__ __forceinline__ float row_move(float v, float old = 0.0f) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, old), __builtin_bit_cast(int, v),
+                                                               CTRL, 0xf, BANKS, true));
+}
+template <int CTRL, int BANKS = 0xf>
+__device__ __forceinline__ double row_move(double v, double old = 0.0) {
+  const uint2 x = __builtin_bit_cast(uint2, v), o = __builtin_bit_cast(uint2, old);
+  return __builtin_bit_cast(double, uint2{(unsigned)__builtin_amdgcn_update_dpp((int)o.x, (int)x.x, CTRL, 0xf, BANKS, true),
+                                          (unsigned)__builtin_amdgcn_update_dpp((int)o.y, (int)x.y, CTRL, 0xf, BANKS, true)});
+}
+constexpr int ROW_SHL = 0x100, ROW_SHR = 0x110, ROW_NEWBCAST = 0x150;
+// the value OFF slices before this lane's (BACK: after it), 0 beyond the segment
+template <int LSEG, bool BACK, int OFF, typename R>
+__device__ __forceinline__ R seg_shift(R v, int s) {
+  const int src = BACK ? s + OFF : s - OFF;
+  const bool inside = src >= 0 && src < LSEG;
+  if constexpr (LSEG <= 16) {
+    const R t = row_move<(BACK ? ROW_SHL : ROW_SHR) + OFF>(v);
+    return LSEG == 16 || inside ? t : R(0);
+  } else {
+    const R t = seg_shfl<LSEG>(v, src & (LSEG - 1));
+    return inside ? t : R(0);
+  }
+}
+// the value of the segment's last (BACK: first) slice
 template <int LSEG, bool BACK, typename R>
-__device__ __forceinline__ void seg_inverse(cx<R>* v, int s, const FifthChir<R>& c, R m) {
+__device__ __forceinline__ R seg_end(R v) {
+  if constexpr (LSEG == 16) return row_move<ROW_NEWBCAST + (BACK ? 0 : 15)>(v);
+  else if constexpr (LSEG == 8)
+    return row_move<ROW_NEWBCAST + (BACK ? 8 : 15), 0xc>(v, row_move<ROW_NEWBCAST + (BACK ? 0 : 7), 0x3>(v));
+  else return seg_shfl<LSEG>(v, BACK ? 0 : LSEG - 1);
+}
+
+// a^n, 1 <= n <= LSEG
+template <int LSEG, typename R>
+__device__ __forceinline__ R power(R a, int n) {
+  R p = (n & 1) ? a : R(1);
+#pragma unroll
+  for (int bit = 2; bit <= LSEG; bit <<= 1) {
+    a *= a;
+    p = (n & bit) ? p * a : p;
+  }
+  return p;
+}
+
+// the scan's steps from OFF on, ap = a^OFF
+template <int LSEG, bool BACK, int OFF, typename R>
+__device__ __forceinline__ void seg_scan(cx<R>* v, int s, R ap) {
+#pragma unroll
+  for (int k = 0; k < 6; ++k) {
+    const R tr = seg_shift<LSEG, BACK, OFF>(v[k].re, s), ti = seg_shift<LSEG, BACK, OFF>(v[k].im, s);
+    v[k] = {fma(ap, tr, v[k].re), fma(ap, ti, v[k].im)};
+  }
+  if constexpr (2 * OFF < LSEG) seg_scan<LSEG, BACK, 2 * OFF>(v, s, ap * ap);
+}
+
+// (1 - a S_d)^-1 on six components
+template <int LSEG, bool BACK, typename R>
+__device__ __forceinline__ void seg_inverse(cx<R>* v, int s, const FifthChir<R>& c) {
   if constexpr (std::is_same<R, float>::value && LSEG == 16) {
     const R a2 = c.a * c.a, a4 = a2 * a2, a8 = a4 * a4;
-    const int d = BACK ? 15 - s : s;  // slices before the wrap
-    row_rotate_steps<BACK>(v, d >= 1 ? c.a : -m * c.a, d >= 2 ? a2 : -m * a2, d >= 4 ? a4 : -m * a4,
-                           d >= 8 ? a8 : -m * a8);
+    row_scan_close<BACK>(v, c.a, a2, a4, a8, -c.corr * power<LSEG>(c.a, BACK ? LSEG - s : s + 1));
+  } else if constexpr (std::is_same<R, float>::value && LSEG == 8) {
+    const R a2 = c.a * c.a, a4 = a2 * a2;
+    half_row_scan_close<BACK>(v, c.a, a2, a4, -c.corr * power<LSEG>(c.a, BACK ? LSEG - s : s + 1));
   } else if constexpr (std::is_same<R, float>::value && LSEG == 32) {
     const R a2 = c.a * c.a, a4 = a2 * a2, a8 = a4 * a4, a16 = a8 * a8;
-    row_shift_steps<BACK>(v, c.a, a2, a4, a8);
+    row_scan<BACK>(v, c.a, a2, a4, a8);
     // carries: c0 enters the row that holds the wrap, c1 the other; with n, f the near and far
     // rows' end values (the row entered first is the far one's successor across the wrap)
     //   c0 = -m (f + a^16 n) / den,  c1 = (n - m a^16 f) / den,  den = 1 + m a^32
@@ -386,17 +480,12 @@ __device__ __forceinline__ void seg_inverse(cx<R>* v, int s, const FifthChir<R>&
       v[k] = {fma(kf, fr, fma(kn, nr, v[k].re)), fma(kf, fi, fma(kn, ni, v[k].im))};
     }
   } else {
-    R ap = c.a;
+    seg_scan<LSEG, BACK, 1>(v, s, c.a);
+    const R w = -c.corr * power<LSEG>(c.a, BACK ? LSEG - s : s + 1);
 #pragma unroll
-    for (int off = 1; off < LSEG; off <<= 1) {
-      const int src = BACK ? s + off : s - off;
-      const R f = (src < 0 || src >= LSEG) ? -m * ap : ap;
-#pragma unroll
-      for (int k = 0; k < 6; ++k) {
-        const R tr = seg_shfl<LSEG>(v[k].re, src & (LSEG - 1)), ti = seg_shfl<LSEG>(v[k].im, src & (LSEG - 1));
-        v[k] = {fma(f, tr, v[k].re), fma(f, ti, v[k].im)};
-      }
-      ap *= ap;
+    for (int k = 0; k < 6; ++k) {
+      const R er = seg_end<LSEG, BACK>(v[k].re), ei = seg_end<LSEG, BACK>(v[k].im);
+      v[k] = {fma(w, er, v[k].re), fma(w, ei, v[k].im)};
     }
   }
 }
@@ -433,11 +522,10 @@ __device__ __forceinline__ void fifth_scan_apply(cx<R> v[12], int s, const Fifth
     const FifthChir<R> c = e.ch[ch];
     if (!__builtin_amdgcn_readfirstlane(c.has_inv)) continue;
     cx<R>* vc = v + ch * 6;
-    const R u = (std::is_same<R, float>::value && LSEG == 32) ? c.inv_alpha : c.inv_alpha * c.inv_den;
 #pragma unroll
-    for (int k = 0; k < 6; ++k) vc[k] = u * vc[k];
-    if (__builtin_amdgcn_readfirstlane(c.d2) < 0) seg_inverse<LSEG, false, R>(vc, s, c, e.m);
-    else seg_inverse<LSEG, true, R>(vc, s, c, e.m);
+    for (int k = 0; k < 6; ++k) vc[k] = c.inv_alpha * vc[k];
+    if (__builtin_amdgcn_readfirstlane(c.d2) < 0) seg_inverse<LSEG, false, R>(vc, s, c);
+    else seg_inverse<LSEG, true, R>(vc, s, c);
   }
 }
 
