@@ -161,8 +161,7 @@ int dwf_dslash(dwf_ctx* ctx, const dwf_params* p, const void* U, const void* in,
                int dagger);
 
 /* The same for the Moebius operator D'_DW(m) with p->b, p->c (Sec. 4); op HOP
- * applies H (b + c S~).  In FP64 and FP32, above 32768 5D sites, b + c S~ is applied in a pass
- * into the context's workspace (one half field). */
+ * applies H (b + c S~). */
 int mobius_dslash(dwf_ctx* ctx, const dwf_params* p, const void* U, const void* in, void* out, int op,
                   int parity, int dagger);
 

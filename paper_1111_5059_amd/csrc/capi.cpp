@@ -114,20 +114,11 @@ int dslash_t(dwf_ctx* ctx, const dwf_params& p, const void* U, const void* in, v
   Op<P> o(ctx, g, p, U);
   const int Ls = p.Ls;
   const size_t hb = half_bytes<P>(g->nsites, Ls);
-  // room for F psi (Moebius operators in FP64 and FP32 storage, see Op::input_factor)
-  auto factor_room = [&]() {
-    if (!o.moebius || sizeof(typename P::S) < 8) return Half<P>{nullptr, nullptr};
-    return half_view<P>(ws_get(ctx, "dslash.t2", hb), g->nsites, Ls);
-  };
   switch (op) {
     case DWF_OP_HOP: {
       // H F in (or (H F)^dag = F^dag H^dag in)
-      if (!dagger) {
-        const CHalf<P> src = chalf_view<P>(in, g->nsites, Ls);
-        const Half<P> f = factor_room();
-        const bool done = o.input_factor(src, f);
-        o.hop(parity, done ? cv(f) : src, half_view<P>(out, g->nsites, Ls), false, !done, 1.0, nullptr);
-      } else
+      if (!dagger) o.hop(parity, chalf_view<P>(in, g->nsites, Ls), half_view<P>(out, g->nsites, Ls), false, true, 1.0, nullptr);
+      else
         o.hop(parity, chalf_view<P>(in, g->nsites, Ls), half_view<P>(out, g->nsites, Ls), true, false, 1.0,
               o.moebius ? o.em(E_FDAG) : nullptr);
       return DWF_OK;
@@ -147,7 +138,7 @@ int dslash_t(dwf_ctx* ctx, const dwf_params& p, const void* U, const void* in, v
       const char* ib = reinterpret_cast<const char*>(in);
       char* ob = reinterpret_cast<char*>(out);
       o.full(chalf_view<P>(ib, g->nsites, Ls), chalf_view<P>(ib + hb, g->nsites, Ls), half_view<P>(ob, g->nsites, Ls),
-             half_view<P>(ob + hb, g->nsites, Ls), dagger != 0, dagger ? Half<P>{nullptr, nullptr} : factor_room());
+             half_view<P>(ob + hb, g->nsites, Ls), dagger != 0);
       return DWF_OK;
     }
     case DWF_OP_A:

@@ -292,15 +292,17 @@ struct Op {
     DWF_CHECK_LAUNCH(launch_hop<P>(a, dag, pro && moebius, cfg, ctx->stream));
     if (mark >= 0) timer_end(ctx, mark, hop_bytes(a));
   }
-  // F in for a hop that then runs without the input factor: in tmp where the storage precision is
-  // that of the arithmetic (FP64, FP32), else not at all (the 16-bit formats keep F in registers,
-  // in the hop's prologue, so that it is not rounded).  The prologue triples the neighbour loads of
-  // a hop that its gathers bound; F as a pass of its own is two streamed fields (FP64, Ls = 16, 24^3 x
-  // 64: prologue hop 2.1 ms, plain hop and pass 1.5 ms).  Small fields keep the prologue: up to 32768
-  // 5D sites a hop waits for one round of loads at a time, and a launch costs more than wider loads.
-  // Returns whether tmp holds F in.
+  // F in for a hop that then runs without the input factor (M_prec, which has a field to spare): in tmp
+  // in FP64 above 65536 5D sites, else not at all.  The prologue doubles the components a hop gathers, in
+  // three streams, where F as a pass of its own is two streamed fields (FP64 M_prec, prologue / pass: 16^3 x 32,
+  // Ls = 16 410 / 376 us, Ls = 12 639 / 392 us; n5 = 81920, Ls = 10 81 / 52 us; n5 = 131072, Ls = 16 52 / 53 us; n5 = 65536,
+  // Ls = 16 30 / 35 us, Ls = 32 35 / 39 us).  FP32 gathers half the bytes and mostly lost with the pass (n5 = 98304,
+  // Ls = 12 33 / 37 us, 16^3 x 32 Ls = 16 204 / 216 us).  The 16-bit formats keep F in registers, so that it is
+  // not rounded.  A hop alone and the full operator keep the prologue in every type: fused into the
+  // projection it rounds F psi less often than a stored field does (FP32 H F at Ls = 12: 2.6 % nearer), and
+  // those calls need no workspace.  Returns whether tmp holds F in.
   bool input_factor(CHalf<P> in, Half<P> tmp) const {
-    if (!moebius || !tmp.data || sizeof(S) < 8 || n5() <= 32768) return false;
+    if (!moebius || !tmp.data || P::ID != DWF_FP64 || n5() <= 65536) return false;
     fifth(in, tmp, E_F);
     return true;
   }
@@ -386,9 +388,8 @@ struct Op {
   // full D (or D^dag):  (D psi)_p = A psi_p - 1/2 H F psi_{1-p};  (D^dag psi)_p = A^dag psi_p - 1/2 F^dag H^dag psi_{1-p}
   // A is applied to the hop's axpy operand as it is read (a pass of its own reads and writes every
   // field once more: 6.17 -> 4.33 ms in FP64 at 24^3 x 64, Ls = 32), except beside the epilogue of the
-  // Moebius adjoint and in FP16; tmp_f (optional, Moebius): room for F psi_{1-p}
-  void full(CHalf<P> in_e, CHalf<P> in_o, Half<P> out_e, Half<P> out_o, bool dag,
-            Half<P> tmp_f = {nullptr, nullptr}) const {
+  // Moebius adjoint and in FP16
+  void full(CHalf<P> in_e, CHalf<P> in_o, Half<P> out_e, Half<P> out_o, bool dag) const {
     if (dag && moebius) {
       fifth(in_e, out_e, E_ADAG);
       fifth(in_o, out_o, E_ADAG);
@@ -403,10 +404,8 @@ struct Op {
       hop(1, in_e, out_o, dag, !dag, -0.5, nullptr, cv(out_o), 1.0);
       return;
     }
-    bool f = input_factor(in_o, tmp_f);
-    hop_a(0, f ? cv(tmp_f) : in_o, out_e, dag, !f && !dag, -0.5, in_e);
-    f = input_factor(in_e, tmp_f);
-    hop_a(1, f ? cv(tmp_f) : in_e, out_o, dag, !f && !dag, -0.5, in_o);
+    hop_a(0, in_o, out_e, dag, !dag, -0.5, in_e);
+    hop_a(1, in_e, out_o, dag, !dag, -0.5, in_o);
   }
 };
 

@@ -418,8 +418,7 @@ int solve_full(dwf_ctx* ctx, const dwf_params& p, const void* U64, const void* b
   } else {
     // source preparation
     op.fifth(be, te, E_AINV);                                  // A^-1 b_e
-    const bool f = op.input_factor(cv(te), bp);
-    op.hop(1, f ? cv(bp) : cv(te), to, false, !f, 0.5, nullptr, bo, 1.0);  // b_o - B_oe A^-1 b_e
+    op.hop(1, cv(te), to, false, true, 0.5, nullptr, bo, 1.0);  // b_o - B_oe A^-1 b_e
     op.fifth(cv(to), bp, E_AINV);                              // b'_o
     op.mprec_dag(cv(bp), rhs, te, t2);                         // M^dag b'
     double tol_n = tol;
@@ -429,11 +428,10 @@ int solve_full(dwf_ctx* ctx, const dwf_params& p, const void* U64, const void* b
       if (left <= 0) break;
       normal_solve(ctx, p, U64, cv(rhs), xo, tol_n, left, delta, tag + ".cg", &st);
       // x_e = A^-1 (b_e - B_eo x_o)
-      const bool f = op.input_factor(cv(xo), t2);
-      op.hop(0, f ? cv(t2) : cv(xo), te, false, !f, 0.5, nullptr, be, 1.0);
+      op.hop(0, cv(xo), te, false, true, 0.5, nullptr, be, 1.0);
       op.fifth(cv(te), xe, E_AINV);
       // true residual of the full system
-      op.full(cv(xe), cv(xo), re, ro, false, t2);
+      op.full(cv(xe), cv(xo), re, ro, false);
       DWF_CHECK_LAUNCH(launch_axpby<P64>(1.0, be, -1.0, re, n5, Ls, s));
       DWF_CHECK_LAUNCH(launch_axpby<P64>(1.0, bo, -1.0, ro, n5, Ls, s));
       const double r2 = norm2_sync<P64>(ctx, cv(re), g, Ls) + norm2_sync<P64>(ctx, cv(ro), g, Ls);
@@ -1155,8 +1153,7 @@ int solve_batched(dwf_ctx* ctx, int nrhs, const dwf_params* P, const void* const
     b2[k] = norm2_sync<P64>(ctx, be, B.g, Ls) + norm2_sync<P64>(ctx, bo, B.g, Ls);
     if (!std::isfinite(b2[k])) throw Error{DWF_ERR_NAN, "non-finite source"};
     B.op64->fifth(be, te, E_AINV);
-    const bool f = B.op64->input_factor(cv(te), bp);
-    B.op64->hop(1, f ? cv(bp) : cv(te), to, false, !f, 0.5, nullptr, bo, 1.0);
+    B.op64->hop(1, cv(te), to, false, true, 0.5, nullptr, bo, 1.0);
     B.op64->fifth(cv(to), bp, E_AINV);
     B.op64->mprec_dag(cv(bp), rhs, te, t2);
     (void)n5;
@@ -1212,11 +1209,9 @@ int solve_batched(dwf_ctx* ctx, int nrhs, const dwf_params* P, const void* const
       Half<P64> te = hview<P64>(ws_get(ctx, "batchfull.se", hb), B.g, Ls);
       void* rf = ws_get(ctx, "batchfull.rfull", 2 * hb);
       Half<P64> re = hview<P64>(rf, B.g, Ls), ro = hview<P64>(reinterpret_cast<char*>(rf) + hb, B.g, Ls);
-      Half<P64> t2 = hview<P64>(ws_get(ctx, "batchfull.t2", hb), B.g, Ls);
-      const bool f = B.op64->input_factor(cv(B.x), t2);
-      B.op64->hop(0, f ? cv(t2) : cv(B.x), te, false, !f, 0.5, nullptr, be, 1.0);
+      B.op64->hop(0, cv(B.x), te, false, true, 0.5, nullptr, be, 1.0);
       B.op64->fifth(cv(te), xe, E_AINV);
-      B.op64->full(cv(xe), cv(B.x), re, ro, false, t2);
+      B.op64->full(cv(xe), cv(B.x), re, ro, false);
       DWF_CHECK_LAUNCH(launch_axpby<P64>(1.0, be, -1.0, re, n5, Ls, s));
       DWF_CHECK_LAUNCH(launch_axpby<P64>(1.0, bo, -1.0, ro, n5, Ls, s));
       const double r2 = norm2_sync<P64>(ctx, cv(re), B.g, Ls) + norm2_sync<P64>(ctx, cv(ro), B.g, Ls);
@@ -1314,8 +1309,7 @@ int madwf(dwf_ctx* ctx, const dwf_params& pt, const dwf_params& pi, const void* 
     for (int par = 0; par < 2; ++par)
       DWF_CHECK_LAUNCH(launch_slice_copy(CH(c, par, L, hb), L, 0, H(cp, par, Lp, hbp), Lp, 0, 1.0, ns, s));
     pshift(cp, zp, 0, Lp, hbp);
-    opi1.full(CH(zp, 0, Lp, hbp), CH(zp, 1, Lp, hbp), H(rp, 0, Lp, hbp), H(rp, 1, Lp, hbp), false,
-              H(yp, 0, Lp, hbp));
+    opi1.full(CH(zp, 0, Lp, hbp), CH(zp, 1, Lp, hbp), H(rp, 0, Lp, hbp), H(rp, 1, Lp, hbp), false);
     // D'(m) z = rhs'
     DWF_CHECK_LAUNCH(launch_zero(zp, 2 * hbp, s));
     std::memset(&si, 0, sizeof(si));

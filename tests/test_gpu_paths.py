@@ -256,3 +256,45 @@ def test_recurrence_is_as_accurate_as_its_steps(env, Ls, prec, b, c, m):
         err["host"] += float(np.sum((host.astype(np.longdouble) - exact) ** 2))
         err["gpu"] += float(np.sum((parts(got, flip).astype(np.longdouble) - exact) ** 2))
     assert err["gpu"] <= 1.02 ** 2 * err["host"], (err["gpu"] / err["host"]) ** 0.5
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("Ls", [12, 16])
+def test_moebius_hop_and_operator_use_no_workspace(env, prec, Ls):
+    """H F and D of the Moebius operator need the context's tables only: with the workspace released
+    they can be captured in a graph (nothing is allocated), and the graph holds no pointer into a
+    workspace that a later call may move: its replays, with the workspace in use between them, give
+    the eager results bit for bit.  Above and below 65536 5D sites."""
+    import torch
+    dwf, _ = env
+    P = dwf.PREC_NAMES[prec]
+    stream = torch.cuda.Stream()
+    with torch.cuda.stream(stream):
+        ctx = dwf.Context(stream.cuda_stream)
+        for dims in ((4, 4, 4, 6), (8, 8, 8, 24)):
+            lat = dwf.Lattice(ctx, dims, Ls, mass=0.2, b=1.5, c=0.5)
+            Ug, p = lat.pack_gauge(synth.random_links(dims, 0.5, 930), P), lat.params(P)
+            src = lat.pack(synth.gaussian_spinor(dims, Ls, 931), dwf.KIND_FULL, P)
+            odd = lat.pack(synth.gaussian_spinor(dims, Ls, 932), dwf.KIND_ODD, P)
+            full, even, other = lat.zeros(dwf.KIND_FULL, P), lat.zeros(dwf.KIND_EVEN, P), lat.zeros(dwf.KIND_ODD, P)
+
+            def apply():
+                dwf.mobius_dslash(ctx, p, Ug, odd, even, dwf.OP_HOP, 0, False)
+                dwf.mobius_dslash(ctx, p, Ug, src, full, dwf.OP_FULL, 0, False)
+
+            apply()
+            stream.synchronize()
+            want = full.clone(), even.clone()
+            ctx.release()
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph, stream=stream):
+                apply()
+            for _ in range(3):
+                full.zero_()
+                even.zero_()
+                dwf.mobius_dslash(ctx, p, Ug, odd, other, dwf.OP_MPREC, 1, True)
+                graph.replay()
+                stream.synchronize()
+                assert torch.equal(full, want[0]) and torch.equal(even, want[1])
+                ctx.release()
+        ctx.close()
