@@ -403,8 +403,9 @@ static std::vector<double> invert_dense(std::vector<double> M, int n) {
   return I;
 }
 
-// Table layout: [slot][chirality][Ls][Ls] matrices, then the Moebius coefficients b_s, c_s
-// (2 Ls values; the constants repeated when not s-dependent), in the storage's real type.
+// Table layout: [slot][chirality][Ls][Ls] matrices, then the Moebius coefficients b_s, c_s and A's alpha_s =
+// b_s d + 1, beta_s = c_s d - 1 (4 Ls values; the constants repeated when not s-dependent), formed in FP64 and
+// rounded once to the storage's real type.
 // With s-dependent coefficients A = diag(alpha_s) + diag(beta_s) S and F = diag(b_s) + diag(c_s) S
 // (row s carries the coefficients of slice s), and A^-1 is computed numerically.
 const void* fifth_matrices(dwf_ctx* ctx, int Ls, double M5, double m, double b, double c, int prec,
@@ -433,10 +434,12 @@ const void* fifth_matrices(dwf_ctx* ctx, int Ls, double M5, double m, double b, 
   const double z = sdep ? 0.0 : beta / alpha;
   const double denom = sdep ? 1.0 : alpha * (1.0 + m * std::pow(-z, Ls));
   if (std::fabs(denom) < 1e-300) throw Error{DWF_ERR_ARG, "singular fifth-dimension block A"};
-  std::vector<double> table(size_t(E_COUNT) * 2 * n * n + 2 * n, 0.0);
+  std::vector<double> table(size_t(E_COUNT) * 2 * n * n + 4 * n, 0.0);
   for (int s = 0; s < n; ++s) {
     table[size_t(E_COUNT) * 2 * n * n + s] = bv[s];
     table[size_t(E_COUNT) * 2 * n * n + n + s] = cv[s];
+    table[size_t(E_COUNT) * 2 * n * n + 2 * n + s] = bv[s] * d + 1.0;
+    table[size_t(E_COUNT) * 2 * n * n + 3 * n + s] = cv[s] * d - 1.0;
   }
   for (int ch = 0; ch < 2; ++ch) {
     const std::vector<double> S = shift_matrix(Ls, m, ch);

@@ -658,9 +658,9 @@ __device__ __forceinline__ void axpy_x_op(const HopArgs<P>& a, long x, int s, in
     const bool wrap = sn < 0 || sn >= Ls;
     sn = sn < 0 ? Ls - 1 : sn >= Ls ? 0 : sn;
     R xa = a.xa, xb = a.xb;
-    if (a.pbs) {
-      xa = a.pbs[s] * a.xdd + R(1);
-      xb = a.pcs[a.x_dir < 0 ? s : sn] * a.xdd - R(1);
+    if (a.xas) {
+      xa = a.xas[s];
+      xb = a.xbs[a.x_dir < 0 ? s : sn];
     }
     if (wrap) xb = -a.pm * xb;
     cx<R> xv[6], nv[6];

@@ -45,11 +45,13 @@ struct HopArgs {
   typename P::R ax;
   // x_dir != 0 (launches without epilogue or fused CG step): the axpy operand is X . x with the
   // bidiagonal site-local operator X = xa + xb S, S taking slice s + x_dir in chirality 0 and
-  // s - x_dir in chirality 1 (-pm across the boundary); with s-dependent coefficients (pbs, pcs
-  // given) xa = b_s xdd + 1 and xb = c_s' xdd - 1, s' the row of the untransposed operator (x_dir -1:
-  // s; +1, the adjoint: the slice read)
+  // s - x_dir in chirality 1 (-pm across the boundary); with tables xas, xbs (Ls values each) the
+  // coefficients are xas[s] and xbs[s'], s' the row of the untransposed operator (x_dir -1: s; +1, the
+  // adjoint: the slice read)
   int x_dir = 0;
-  typename P::R xa = 0, xb = 0, xdd = 0;
+  typename P::R xa = 0, xb = 0;
+  const typename P::R* xas = nullptr;
+  const typename P::R* xbs = nullptr;
   // x_es2 != 0 (fused CG step, scan epilogue shapes only): the axpy operand is es2 . x, the
   // bidiagonal site-local operator applied to x in registers (the CG hop then reads A^-dag q, which it
   // turns back into q = A^dag (A^-dag q), and q itself need not be stored); interleaved right-

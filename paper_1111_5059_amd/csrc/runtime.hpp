@@ -175,7 +175,7 @@ struct Op {
   bool sdep;     // s-dependent Moebius coefficients
   const S* U[2];
   const R* E;
-  const R* coef_b;  // device b_s, c_s (Ls each), in the table after the matrices
+  const R* coef_b;  // device b_s, c_s (Ls each), in the table after the matrices, then alpha_s, beta_s
   const R* coef_c;
   FifthScan<R> es[E_COUNT];  // the slots in recurrence form
   bool scan_ok;
@@ -286,7 +286,10 @@ struct Op {
     a.x_dir = dag ? +1 : -1;
     a.xa = R(xa);
     a.xb = R(xb);
-    a.xdd = R(4.0 - M5);
+    if (sdep) {  // (alpha_s, beta_s, in the table after b_s, c_s)
+      a.xas = coef_c + Ls;
+      a.xbs = coef_c + 2 * Ls;
+    }
     long mark = -1;
     if (ctx->timer.on) mark = timer_begin(ctx, hop_name(a, dag, pro && moebius, cfg));
     DWF_CHECK_LAUNCH(launch_hop<P>(a, dag, pro && moebius, cfg, ctx->stream));

@@ -298,3 +298,38 @@ def test_moebius_hop_and_operator_use_no_workspace(env, prec, Ls):
                 assert torch.equal(full, want[0]) and torch.equal(even, want[1])
                 ctx.release()
         ctx.close()
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32"])
+@pytest.mark.parametrize("dag", [False, True])
+def test_operator_coefficients_are_rounded_once(env, prec, dag):
+    """D with coefficients per slice on zero links is A = alpha_s + beta_s S~.  On a field of one slice
+    the result's slices are that slice times alpha_s, beta_s (-m beta_s across the boundary); the best
+    fit of the factor averages the products' own rounding away and leaves the factor's: at most half a
+    unit, 2^-24 (2^-53) relative, and as much again where -m multiplies it.  (10^4 components: the
+    average's own scatter is a hundredth of a unit.)"""
+    dwf, ctx = env
+    P = dwf.PREC_NAMES[prec]
+    dims, Ls, m, d = (4, 4, 4, 6), 7, 0.3, 4.0 - 1.8
+    half = 2.0 ** (-53 if prec == "fp64" else -24)
+    w = 1.5 + 0.5 * np.sin(np.arange(Ls))
+    b_s, c_s = (w + 1) / 2, (w - 1) / 2
+    lat = dwf.Lattice(ctx, dims, Ls, mass=m, b_s=b_s, c_s=c_s)
+    Ug, p = lat.pack_gauge(np.zeros_like(synth.random_links(dims, 0.5, 940)), P), lat.params(P)
+    for s in range(Ls):
+        psi = np.zeros_like(synth.gaussian_spinor(dims, Ls, 941))
+        psi[s] = synth.gaussian_spinor(dims, Ls, 941 + s)[s]
+        src, dst = lat.pack(psi, dwf.KIND_FULL, P), lat.empty(dwf.KIND_FULL, P)
+        x = lat.unpack_np(src, dwf.KIND_FULL, P)[s].astype(np.clongdouble)
+        dwf.mobius_dslash(ctx, p, Ug, src, dst, dwf.OP_FULL, 0, dag)
+        got = lat.unpack_np(dst, dwf.KIND_FULL, P).astype(np.clongdouble)
+        for ch, spins in ((0, slice(0, 2)), (1, slice(2, 4))):
+            n = s + (1 if ch == 0 else -1) * (-1 if dag else 1)  # the slice that reads slice s
+            wrap = n < 0 or n >= Ls
+            n %= Ls
+            row = s if dag else n
+            want = {s: b_s[s] * d + 1, n: (c_s[row] * d - 1) * (-m if wrap else 1)}  # (formed in FP64)
+            for t, f in want.items():
+                xs = x[..., spins, :]
+                fit = np.sum((got[t][..., spins, :] * xs.conj()).real) / np.sum(np.abs(xs) ** 2)
+                assert abs(fit / np.longdouble(f) - 1) < half * (2.1 if wrap and t == n else 1.1), (s, ch, t)
