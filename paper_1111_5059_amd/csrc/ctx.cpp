@@ -365,6 +365,14 @@ bool fifth_scan(int Ls, double M5, double m, double b, double c, int slot, Fifth
       case E_F_AINV: q.a1 = b; q.b1 = c; q.d1 = dS; q.has_inv = 1; q.d2 = dS; break;
       default: return false;
     }
+    // both factors: 1/alpha goes into the bidiagonal one, which saves a rounding of every value (FP32 M_prec,
+    // b = 1.5, Ls = 16: 7.52e-8 from the exact result with F applied in the second hop, 7.60e-8 with F A^-1
+    // in the first and 1/alpha apart, 7.01e-8 so)
+    if (q.has_inv && q.b1 != 0.0) {
+      q.a1 *= q.inv_alpha;
+      q.b1 *= q.inv_alpha;
+      q.inv_alpha = 1.0;
+    }
     e.ch[ch] = q;
   }
   *out = e;

@@ -296,16 +296,18 @@ struct Op {
     if (mark >= 0) timer_end(ctx, mark, hop_bytes(a));
   }
   // F in for a hop that then runs without the input factor (M_prec, which has a field to spare): in tmp
-  // in FP64 above 65536 5D sites, else not at all.  The prologue doubles the components a hop gathers, in
-  // three streams, where F as a pass of its own is two streamed fields (FP64 M_prec, prologue / pass: 16^3 x 32,
-  // Ls = 16 410 / 376 us, Ls = 12 639 / 392 us; n5 = 81920, Ls = 10 81 / 52 us; n5 = 131072, Ls = 16 52 / 53 us; n5 = 65536,
-  // Ls = 16 30 / 35 us, Ls = 32 35 / 39 us).  FP32 gathers half the bytes and mostly lost with the pass (n5 = 98304,
-  // Ls = 12 33 / 37 us, 16^3 x 32 Ls = 16 204 / 216 us).  The 16-bit formats keep F in registers, so that it is
-  // not rounded.  A hop alone and the full operator keep the prologue in every type: fused into the
-  // projection it rounds F psi less often than a stored field does (FP32 H F at Ls = 12: 2.6 % nearer), and
-  // those calls need no workspace.  Returns whether tmp holds F in.
+  // in FP64 above 65536 5D sites and in FP32 above 131072 where F is a recurrence, else not at all.  The
+  // prologue doubles the components a hop gathers, in three streams, where F as a pass of its own is two
+  // streamed fields (M_prec, prologue / pass.  FP64: 16^3 x 32, Ls = 16 410 / 376 us, Ls = 12 639 / 392 us; n5 = 81920,
+  // Ls = 10 81 / 52 us; n5 = 131072, Ls = 16 52 / 53 us; n5 = 65536, Ls = 16 30 / 35 us, Ls = 32 35 / 39 us.  FP32: 24^3 x
+  // 64, Ls = 16 1499 / 1468 us; 12^3 x 24, Ls = 16 79 / 74 us; n5 = 131072, Ls = 16 34.5 / 34.4 us; dense, n5 = 98304,
+  // Ls = 12 33 / 37 us; of 15 sizes one lost, 16^3 x 32, Ls = 16 205 / 217 us).  The 16-bit formats keep F in
+  // registers, so that it is not rounded.  A hop alone and the full operator keep the prologue in every
+  // type: fused into the projection it rounds F psi less often than a stored field does (FP32 H F at
+  // Ls = 12: 2.6 % nearer), and those calls need no workspace.  Returns whether tmp holds F in.
   bool input_factor(CHalf<P> in, Half<P> tmp) const {
-    if (!moebius || !tmp.data || P::ID != DWF_FP64 || n5() <= 65536) return false;
+    if (!moebius || !tmp.data || sizeof(S) < 8) return false;
+    if (P::ID == DWF_FP64 ? n5() <= 65536 : n5() <= 131072 || !scan_ok || (Ls != 8 && Ls != 16 && Ls != 32)) return false;
     fifth(in, tmp, E_F);
     return true;
   }
@@ -351,7 +353,7 @@ struct Op {
   // prologue and the even field stored in between is F A^-1 (...).  In bf16 it is A^-1 (...), and the
   // second hop applies F: F enlarges the rounding of the stored field less than its components, and with
   // F A^-1 stored the result was 1.2-1.6 % further from the exact one (in FP16, whose prologue itself
-  // works in FP16, 7 % nearer; FP32 rounds no more often either way).
+  // works in FP16, 7 % nearer, and in FP32 7-10 %).
   void mprec(CHalf<P> in, Half<P> out, Half<P> tmp_e, double* partials = nullptr,
              Half<P> ainvdag_out = {nullptr, nullptr}, Half<P> tmp_f = {nullptr, nullptr}) const {
     constexpr bool FOLD = P::ID != DWF_BF16;
