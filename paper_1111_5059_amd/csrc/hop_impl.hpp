@@ -1044,8 +1044,12 @@ __device__ __forceinline__ void hop_split_body(const HopArgs<P>& a, long bid, in
   }
   if constexpr (EPI >= 2) fifth_scan_apply<(LS > 0 ? LS : 1)>(acc[0], s, a.es);
   if constexpr (EPI == 1) {
-    // dense matrices along s through LDS (this wave's own accesses, in order)
+    // dense matrices along s through LDS, by this wave alone: every lane's partial sums are read
+    // before any lane's row overwrites them, and every row is written before any is read
     cx<R>* rows = reinterpret_cast<cx<R>*>(smem_raw) + lsite * 12 * Ls;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
     if (active) {
 #pragma unroll
       for (int k = 0; k < 12; ++k) rows[k * Ls + s] = acc[0][k];
