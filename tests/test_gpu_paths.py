@@ -366,3 +366,29 @@ def test_moebius_mprec_with_the_factor_in_the_epilogue(env, Ls, b, c):
     exact = res["fp64"][0]
     err = [np.linalg.norm(r - exact) for r in res["fp32"]]
     assert err[0] <= 1.01 * err[1], err[0] / err[1]
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("shape", ["default", "explicit"])
+def test_5d_hop_reads_neighbouring_slices_only(env, prec, shape):
+    """K takes a site's own 4D parity from slices s - 1 and s + 1, never from s: an infinite component in
+    one slice of one site leaves that slice of that site as it is without it."""
+    dwf, ctx = env
+    P = dwf.PREC_NAMES[prec]
+    dims, Ls, s = (4, 4, 2, 6), 8, 3
+    lat = dwf.Lattice(ctx, dims, Ls, mass=0.2)
+    Ug, p = lat.pack_gauge(synth.random_links(dims, 0.5, 960), P), lat.params(P)
+    psi = synth.gaussian_spinor(dims, Ls, 961)
+    if shape == "explicit":
+        dwf.dwf_tune_set(ctx, P, Ls, 16, 1)
+    try:
+        for dag in (False, True):
+            out = []
+            for v in (0.0, np.inf):
+                psi[s, 2, 1, 1, 3] = v  # one spinor
+                src, dst = lat.pack(psi, dwf.KIND_FULL, P), lat.empty(dwf.KIND_FULL, P)
+                dwf.dwf_dslash_5d(ctx, p, Ug, src, dst, dwf.OP5_HOP, dag)
+                out.append(lat.unpack_np(dst, dwf.KIND_FULL, P)[s, 2, 1, 1, 3])
+            assert np.isfinite(out[0]).all() and np.array_equal(out[0], out[1]), dag
+    finally:
+        dwf.dwf_tune_set(ctx, P, Ls, 0, 0)
