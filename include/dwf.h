@@ -316,9 +316,9 @@ int quotient_force(dwf_ctx* ctx, const dwf_params* p, int nq, const double* mass
  * interleaved along the fifth dimension (Shamir, Ls 8/16/32: the batched solvers use it
  * unless it is switched off; sites_per_block 1 = on, -1 = off, s_per_thread 1, link_lds
  * 0 or 1; the workgroup holds the whole site, 256 / (nrhs Ls) sites).
- * sites_per_block = s_per_thread = 0 restores the default.  The default shape of kernel 0 spreads
- * the eight directions of fields of at most 32768 (16 bit), 49152 (FP64) or 65536 (FP32) 5D
- * sites over the waves of a workgroup; a shape set here is used at every size.
+ * sites_per_block = s_per_thread = 0 restores the default.  The default of kernel 0 spreads the
+ * eight directions of small fields (Ls <= 64; up to a few hundred workgroups of 64 / Ls sites, by
+ * precision and extent) over the waves of a workgroup; a shape set here is used at every size.
  * Rejects shapes the kernel cannot run (more than 256 threads, Ls not divisible
  * by s_per_thread, LDS above 64 KiB, mode 2 outside its shape) with DWF_ERR_ARG. */
 int dwf_tune_set(dwf_ctx* ctx, int kernel_id, int prec, int Ls, int sites_per_block, int s_per_thread,

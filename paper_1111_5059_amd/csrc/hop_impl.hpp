@@ -1256,7 +1256,7 @@ static int launch_hop_t(const HopArgs<P>& a, const LaunchCfg& cfg, hipStream_t s
   }
   if constexpr (NS == 1) {
     constexpr bool LL = !std::is_same<P, P16>::value;
-    if (split_shape<P>(cfg, a.nsites, a.Ls)) {
+    if (split_shape<P>(cfg, a.nsites, a.Ls, PRO, DAG)) {
       const int sp = split_spb(a.Ls);
       void (*k)(HopArgs<P>, int) = hop_kernel<P, LS, NS, DAG, PRO, EPI, LL, CG, false>;
       hipLaunchKernelGGL(k, dim3((unsigned)((a.nsites + sp - 1) / sp)), dim3(256), 3 * 24 * 64 * sizeof(typename P::R), st,

@@ -102,16 +102,30 @@ inline bool stage_shape(const LaunchCfg& cfg, int Ls) {
 }
 
 // Small fields run the hop with its eight directions spread over the four waves of a workgroup
-// (see hop_split_body): default launch shapes, a site's slices in one wave, and at most as many 5D
-// sites as it was faster for (M_prec, us, general / spread: FP32 n5 = 65536 19.7 / 18.7, 131072 29.8 /
-// 29.0; FP64 49152 27.8 / 25.6, 65536 30.6 / 31.4; FP16 32768 11.9 / 10.3, 65536 12.7 / 14.9).
-template <typename P>
-bool split_shape(const LaunchCfg& cfg, long nsites, int Ls) {
-  const long most = sizeof(typename P::S) == 4 ? 32768 : sizeof(typename P::S) == 8 ? 65536 : 49152;
-  return !cfg.tuned && cfg.ns == 1 && !cfg.stage && Ls <= 64 && nsites * Ls <= most;
-}
-// its sites per workgroup
+// (see hop_split_body): default launch shapes, a site's slices in one wave (split_spb sites per
+// workgroup), and at most as many workgroups as it is faster for, about what the chip holds at once:
+// one per CU in FP64 (up to 256 registers), two to four in the other precisions, where the general
+// kernel fills the chip beyond.  The line lies higher for the adjoint hops and for the smallest extents,
+// lower with the Moebius prologue, where the general kernel is slower or faster.
+// (us, general / spread at a number of workgroups.  M_prec: FP64 Ls = 16 192 16.6 / 13.4, 320 16.9 / 18.4, Ls = 24
+// 256 22.6 / 17.5, 432 25.4 / 21.2, 672 25.7 / 28.1, Ls = 2 640 62 / 30; FP32 Ls = 16 512 15.8 / 14.0, 640 15.9 / 16.4, Ls = 33
+// 384 21.9 / 18.1, 1024 22.5 / 25.1, Ls = 2 906 59 / 24; FP16 Ls = 16 500 11.1 / 10.4, Ls = 2 188 13.2 / 10.9, 312 13.5 / 15.1;
+// bf16 Ls = 16 400 16.4 / 12.1.  Its adjoint: FP64 Ls = 16 640 31.1 / 29.3, FP32 Ls = 16 1024 23.4 / 21.4.  Moebius H: FP64
+// Ls = 10 336 9.6 / 10.5; FP16 Ls = 10 405 11.0 / 8.1, Ls = 48 384 6.3 / 7.0.)
 inline int split_spb(int Ls) { return 64 / Ls; }
+template <typename P>
+long split_most(int Ls, bool pro, bool dag) {
+  const bool seg = Ls == 8 || Ls == 16 || Ls == 32;
+  if (sizeof(typename P::S) == 16) return Ls <= 4 ? (pro ? 416 : 640) : dag ? 640 : seg || pro ? 256 : 384;
+  if (sizeof(typename P::S) == 8) return Ls < 8 || (dag && seg) ? 1024 : dag ? 640 : 576;
+  if (P::NORM) return !seg && (Ls < 4 || (pro && Ls >= 24)) ? 256 : 511;
+  return 640;
+}
+template <typename P>
+bool split_shape(const LaunchCfg& cfg, long nsites, int Ls, bool pro, bool dag) {
+  return !cfg.tuned && cfg.ns == 1 && !cfg.stage && Ls <= 64 &&
+         (nsites + split_spb(Ls) - 1) / split_spb(Ls) <= split_most<P>(Ls, pro, dag);
+}
 
 // the launches that apply a site-local operator to the fused CG step's axpy operand
 // (HopArgs::x_es2): one slice per lane, the site's Ls lanes a wave segment, not the LDS-staged

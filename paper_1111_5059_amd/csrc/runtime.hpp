@@ -340,9 +340,10 @@ struct Op {
   bool second_output_ok() const { return scan_ok && cfg.ns == 1 && (Ls == 8 || Ls == 16 || Ls == 32); }
   // ... and the last hop of M^dag q can rebuild q from that second output (q need not be stored)
   bool rebuild_q_ok() const { return second_output_ok() && x_es2_shape<P>(cfg, Ls); }
-  // workgroups of one hop launch (the norm partials it writes)
-  long hop_blocks() const {
-    const int spb = split_shape<P>(cfg, g->nsites, Ls) ? split_spb(Ls) : cfg.spb;
+  // workgroups of one hop launch without prologue, the norm partials it writes (the hops that write them,
+  // the last ones of M_prec and, dag, of M_prec^dag in the solvers, have none)
+  long hop_blocks(bool dag) const {
+    const int spb = split_shape<P>(cfg, g->nsites, Ls, false, dag) ? split_spb(Ls) : cfg.spb;
     return (g->nsites + spb - 1) / spb;
   }
   // M_prec psi = psi - 1/4 A^-1 H_oe (F A^-1) H_eo F psi    (odd -> odd); tmp_f (optional, Moebius):
@@ -466,7 +467,7 @@ struct Op5 {
     const size_t n = size_t(q) * g4->nsites * Ls;
     return {f.data ? f.data + n * 12 : nullptr, f.norm ? f.norm + n : nullptr};
   }
-  long hop_blocks() const { return 2 * ((g4->nsites + cfg.spb - 1) / cfg.spb); }
+  long hop_blocks(bool) const { return 2 * ((g4->nsites + cfg.spb - 1) / cfg.spb); }
   bool second_output_ok() const { return false; }
   bool rebuild_q_ok() const { return false; }
   long n5() const { return gv.nsites * Ls; }

@@ -148,7 +148,7 @@ static int cg_normal(dwf_ctx* ctx, const OpT<P64>& op64, const OpT<Pi>& opi, CHa
   p_update(0.0, rr);
   cur = (cur + 1) % KX;
   double rr_max = rr, rr_true = rr;
-  const long nb_hop = opi.hop_blocks();
+  const int nb_q = int(opi.hop_blocks(false)), nb_r = int(opi.hop_blocks(true));  // norm partials of M p, of M^dag q
   int it = 0;
   while (it < maxit) {
     const Half<Pi> p = pr[cur];
@@ -158,14 +158,14 @@ static int cg_normal(dwf_ctx* ctx, const OpT<P64>& op64, const OpT<Pi>& opi, CHa
     const Half<Pi> q2 = OUT2 ? to : Half<Pi>{nullptr, nullptr};
     if (PRE) opi.mprec_pre(cv(fp), cv(p), q, te, part, q2);
     else opi.mprec(cv(p), q, te, part, q2);
-    DWF_CHECK_LAUNCH(launch_reduce(part, int(nb_hop), 1, sc, S_QQ, 1, s, pend.n));
+    DWF_CHECK_LAUNCH(launch_reduce(part, nb_q, 1, sc, S_QQ, 1, s, pend.n));
     pend.p[pend.n] = cv(p);
     pend.slot[pend.n] = pend.n;
     ++pend.n;
     // r -= alpha M^dag q and |r|^2, fused into the last hop of M^dag q
     opi.mprec_dag_cg(cv(q), to, te, r, sc, part, OUT2, QREB);
     arm_host(ctx, 1);
-    DWF_CHECK_LAUNCH(launch_reduce(part, int(nb_hop), 1, sc, S_RRNEW, 2, s, -1, 1, 0, ctx->h_poll));
+    DWF_CHECK_LAUNCH(launch_reduce(part, nb_r, 1, sc, S_RRNEW, 2, s, -1, 1, 0, ctx->h_poll));
     if (pend.n == KX) flush();
     // the next direction with beta = rr_new / rr from the device, queued before the host has read rr_new:
     // the read hides behind it.  (Where the host decides otherwise, the slot is written again.)
