@@ -663,16 +663,15 @@ __device__ __forceinline__ void axpy_x_op(const HopArgs<P>& a, long x, int s, in
       xb = a.xbs[a.x_dir < 0 ? s : sn];
     }
     if (wrap) xb = -a.pm * xb;
-    // (an operator without a diagonal takes nothing from the slice itself: 0 times it need not be 0)
+    // An operator without a diagonal takes nothing from the slice itself (0 times it need not be 0): the
+    // neighbour twice, each time half, which is exact.  (Selecting 0 per value cost FP64 50 registers.)
     const bool own = a.xas || xa != R(0);
+    if (!own) xa = xb = R(0.5) * xb;
     cx<R> xv[6], nv[6];
     load_half_spinor<P>(a.x, x, own ? s : sn, Ls, ch * 6, xv);
     load_half_spinor<P>(a.x, x, sn, Ls, ch * 6, nv);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      const cx<R> d = {own ? xv[k].re : R(0), own ? xv[k].im : R(0)};
-      acc[ch * 6 + k] = acc[ch * 6 + k] + a.ax * (xa * d + xb * nv[k]);
-    }
+    for (int k = 0; k < 6; ++k) acc[ch * 6 + k] = acc[ch * 6 + k] + a.ax * (xa * xv[k] + xb * nv[k]);
   }
   __builtin_amdgcn_sched_barrier(0);
 }
