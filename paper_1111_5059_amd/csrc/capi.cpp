@@ -117,9 +117,10 @@ int dslash_t(dwf_ctx* ctx, const dwf_params& p, const void* U, const void* in, v
   switch (op) {
     case DWF_OP_HOP: {
       // H F in (or (H F)^dag = F^dag H^dag in)
-      if (!dagger) o.hop(parity, chalf_view<P>(in, g->nsites, Ls), half_view<P>(out, g->nsites, Ls), false, true, 1.0, nullptr);
+      if (!dagger)
+        o.hop_last(parity, chalf_view<P>(in, g->nsites, Ls), half_view<P>(out, g->nsites, Ls), false, true, 1.0, nullptr);
       else
-        o.hop(parity, chalf_view<P>(in, g->nsites, Ls), half_view<P>(out, g->nsites, Ls), true, false, 1.0,
+        o.hop_last(parity, chalf_view<P>(in, g->nsites, Ls), half_view<P>(out, g->nsites, Ls), true, false, 1.0,
               o.moebius ? o.em(E_FDAG) : nullptr);
       return DWF_OK;
     }

@@ -676,6 +676,31 @@ __device__ __forceinline__ void axpy_x_op(const HopArgs<P>& a, long x, int s, in
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// In FP64 and FP32 the streamed operands (axpy operand, residual, outputs) can be read and written
+// non-temporally, which leaves the caches to the gathered spinors.  That pays where the next launch would
+// not find them in a cache anyway: in fields too large for that, and in the last launch of a call
+// (M_prec, hint / none: FP64 n5 = 207360 91 / 84 us, 262144 182 / 216 us, 14155776 -4 to -10 %; FP32 n5 = 524288
+// 111 / 97 us, 737280 112 / 98 us, 1048576 178 / 197 us; D, FP32 n5 = 524288 91 / 107 us).  The 16-bit fields are
+// better kept for the next kernel (fused CG hop +6 % with the hint).
+template <typename P>
+__device__ __forceinline__ bool stream_hint(const HopArgs<P>& a, int Ls) {
+  return a.last || a.nsites * Ls >= (sizeof(typename P::S) == 16 ? 262144 : 786432);
+}
+template <typename P, bool NT>
+__device__ __forceinline__ void load_streamed(bool nt, CHalf<P> f, long x, int s, int Ls, cx<typename P::R> v[12]) {
+  if constexpr (NT) {
+    if (nt) return load_spinor<P, true>(f, x, s, Ls, v);
+  }
+  load_spinor<P>(f, x, s, Ls, v);
+}
+template <typename P, bool NT>
+__device__ __forceinline__ void store_streamed(bool nt, Half<P> f, long x, int s, int Ls, const cx<typename P::R> v[12]) {
+  if constexpr (NT) {
+    if (nt) return store_spinor<P, true>(f, x, s, Ls, v);
+  }
+  store_spinor<P>(f, x, s, Ls, v);
+}
+
 template <typename P, int LS, int NS, bool DAG, bool PRO, int EPI, bool LL, bool CG, bool ST, int RS = 0,
           bool EO5 = false>
 __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pidx, int spb) {
@@ -852,11 +877,16 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
   // the axpy operand through X = xa + xb S, its neighbouring slices read beside it (x_dir)
   constexpr bool XOP = x_op_prec<P>() && !CG && EPI == 0 && RS == 0 && !ST && !EO5;
   constexpr bool XSI = CG && RS > 0 && EPI < 2 && !std::is_same<P, P64>::value;  // per right-hand side
-  // In FP64 and FP32 the streamed operands (axpy operand, residual, outputs) are read and written
-  // non-temporally: they are not used again in this launch, and the L2 is left to the gathered
-  // spinors (24^3 x 64: FP64 Ls = 32 hops -4 to -10 %, FP32 Ls = 16 -2 to -4 %).  The 16-bit
-  // fields are better kept in the caches for the next kernel (fused CG hop +6 % with the hint).
+  // (see stream_hint; the gathered sums are pinned before the choice, else FP64 hops without epilogue hold
+  // the loads across it: 204 VGPRs instead of 152)
   constexpr bool NT = sizeof(typename P::S) >= 8;
+  const bool nt = NT && stream_hint<P>(a, EO5 ? 2 * Ls : Ls);
+  if constexpr (NT && EPI == 0 && !CG) {
+#pragma unroll
+    for (int j = 0; j < NS; ++j)
+#pragma unroll
+      for (int k = 0; k < 12; ++k) asm volatile("" : "+v"(acc[j][k].re), "+v"(acc[j][k].im));
+  }
   double nrm = 0.0;
   if constexpr (XS) __builtin_amdgcn_sched_barrier(0);  // (the operand's loads stay below the gathers: 128 -> 108 VGPRs)
   if (active) {
@@ -873,7 +903,7 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
       }
       if (a.x.data && !x_done) {
         cx<R> xv[12];
-        load_spinor<P, NT>(a.x, x, s, Ls, xv);
+        load_streamed<P, NT>(nt, a.x, x, s, Ls, xv);
         if constexpr (XS) {
           if (a.x_es2) fifth_bidiagonal_apply<(LS > 0 ? LS : 1)>(xv, s, a.es2);
         } else if constexpr (XSI) {
@@ -885,10 +915,10 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
       if constexpr (CG) {
         // r -= alpha v: the CG residual update on the site this thread holds
         cx<R> rv[12];
-        load_spinor<P, NT>(CHalf<P>{a.cg_r.data, a.cg_r.norm}, x, s, Ls, rv);
+        load_streamed<P, NT>(nt, CHalf<P>{a.cg_r.data, a.cg_r.norm}, x, s, Ls, rv);
 #pragma unroll
         for (int k = 0; k < 12; ++k) rv[k] = {rv[k].re - alpha * acc[j][k].re, rv[k].im - alpha * acc[j][k].im};
-        store_spinor<P, NT>(a.cg_r, x, s, Ls, rv);
+        store_streamed<P, NT>(nt, a.cg_r, x, s, Ls, rv);
         if (a.norm_partials) {
 #pragma unroll
           for (int k = 0; k < 12; ++k)
@@ -901,7 +931,7 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
             nrm += double(acc[j][k].re) * double(acc[j][k].re) + double(acc[j][k].im) * double(acc[j][k].im);
         }
         // (no out with a second output: only the norm and out2 are wanted)
-        if (a.out.data) store_spinor<P, NT>(a.out, x, s, Ls, acc[j]);
+        if (a.out.data) store_streamed<P, NT>(nt, a.out, x, s, Ls, acc[j]);
       }
     }
   }
@@ -911,7 +941,7 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
     constexpr int SEG = RS > 0 ? RS : LS;
     if constexpr (RS > 0) fifth_scan_apply<SEG>(acc[0], sr, es_lds[EPI == 3 ? 1 : 0][rhs]);
     else fifth_scan_apply<SEG>(acc[0], s0, a.es2);
-    if (active) store_spinor<P, NT>(a.out2, x, s0, Ls, acc[0]);
+    if (active) store_streamed<P, NT>(nt, a.out2, x, s0, Ls, acc[0]);
   }
   if (a.norm_partials) {
     if constexpr (RS > 0) {

@@ -43,6 +43,8 @@ struct HopArgs {
   int epi_scan = 0;            // es is valid (used when the site's lanes form a wave segment)
   CHalf<P> x;                  // axpy operand (data == nullptr: none)
   typename P::R ax;
+  // last != 0: no launch that follows reads this one's result soon (see stream_hint)
+  int last = 0;
   // x_dir != 0 (launches without epilogue or fused CG step): the axpy operand is X . x with the
   // bidiagonal site-local operator X = xa + xb S, S taking slice s + x_dir in chirality 0 and
   // s - x_dir in chirality 1 (-pm across the boundary); with tables xas, xbs (Ls values each) the

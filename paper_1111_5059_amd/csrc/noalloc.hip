@@ -160,6 +160,7 @@ static int noalloc_t(dwf_ctx* ctx, const dwf_params& p, const void* U, const voi
       a.xb = R(p.c * d - 1.0);
     }
     a.norm_partials = nullptr;
+    a.last = op != DWF_OP_MPREC;
     DWF_CHECK_LAUNCH(launch_hop<P>(a, dag, pro && moebius, cfg, st));
   };
   auto fifth = [&](CHalf<P> src, Half<P> dst, int slot) {

@@ -264,15 +264,21 @@ struct Op {
                                      : fb * (1 + (a.out.data ? 1 : 0) + (xin ? 1 : 0) + (a.out2.data ? 1 : 0));
     return double(n5()) * bytes + double(g->nsites) * 72 * sizeof(S);
   }
-  // out2 (optional): slot2 applied to the final result, a second output of the same launch
+  // out2 (optional): slot2 applied to the final result, a second output of the same launch; last: HopArgs::last
   void hop(int out_par, CHalf<P> in, Half<P> out, bool dag, bool pro, double scale, const R* epi,
            CHalf<P> x = {nullptr, nullptr}, double ax = 0.0, double* partials = nullptr,
-           const CgStep& cg = CgStep(), Half<P> out2 = {nullptr, nullptr}, int slot2 = 0) const {
-    const HopArgs<P> a = hop_args(out_par, in, out, epi, scale, x, ax, partials, cg, out2, slot2);
+           const CgStep& cg = CgStep(), Half<P> out2 = {nullptr, nullptr}, int slot2 = 0, bool last = false) const {
+    HopArgs<P> a = hop_args(out_par, in, out, epi, scale, x, ax, partials, cg, out2, slot2);
+    a.last = last;
     long mark = -1;
     if (ctx->timer.on) mark = timer_begin(ctx, hop_name(a, dag, pro && moebius, cfg));
     DWF_CHECK_LAUNCH(launch_hop<P>(a, dag, pro && moebius, cfg, ctx->stream));
     if (mark >= 0) timer_end(ctx, mark, hop_bytes(a));
+  }
+  // out = epi . (scale H [F] in) [+ x], the last launch of a call
+  void hop_last(int out_par, CHalf<P> in, Half<P> out, bool dag, bool pro, double scale, const R* epi,
+                CHalf<P> x = {nullptr, nullptr}) const {
+    hop(out_par, in, out, dag, pro, scale, epi, x, 1.0, nullptr, CgStep(), Half<P>{nullptr, nullptr}, 0, true);
   }
   // ... with the axpy operand A x (dag: A^dag x): out = A x + scale H [F] in
   void hop_a(int out_par, CHalf<P> in, Half<P> out, bool dag, bool pro, double scale, CHalf<P> x) const {
@@ -283,6 +289,7 @@ struct Op {
   void hop_x(int out_par, CHalf<P> in, Half<P> out, bool dag, bool pro, double scale, CHalf<P> x, double xa,
              double xb) const {
     HopArgs<P> a = hop_args(out_par, in, out, nullptr, scale, x, 1.0);
+    a.last = 1;
     a.x_dir = dag ? +1 : -1;
     a.xa = R(xa);
     a.xb = R(xb);
@@ -399,15 +406,15 @@ struct Op {
     if (dag && moebius) {
       fifth(in_e, out_e, E_ADAG);
       fifth(in_o, out_o, E_ADAG);
-      hop(0, in_o, out_e, true, false, -0.5, em(E_FDAG), cv(out_e), 1.0);
-      hop(1, in_e, out_o, true, false, -0.5, em(E_FDAG), cv(out_o), 1.0);
+      hop_last(0, in_o, out_e, true, false, -0.5, em(E_FDAG), cv(out_e));
+      hop_last(1, in_e, out_o, true, false, -0.5, em(E_FDAG), cv(out_o));
       return;
     }
     if (!x_op_prec<P>()) {
       fifth(in_e, out_e, dag ? E_ADAG : E_A);
       fifth(in_o, out_o, dag ? E_ADAG : E_A);
-      hop(0, in_o, out_e, dag, !dag, -0.5, nullptr, cv(out_e), 1.0);
-      hop(1, in_e, out_o, dag, !dag, -0.5, nullptr, cv(out_o), 1.0);
+      hop_last(0, in_o, out_e, dag, !dag, -0.5, nullptr, cv(out_e));
+      hop_last(1, in_e, out_o, dag, !dag, -0.5, nullptr, cv(out_o));
       return;
     }
     hop_a(0, in_o, out_e, dag, !dag, -0.5, in_e);
