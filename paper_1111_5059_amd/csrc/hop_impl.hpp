@@ -47,14 +47,17 @@ inline size_t hop_lds_bytes(const LaunchCfg& cfg, int Ls, bool epi) {
   return b;
 }
 
-// The precisions whose dense-epilogue hops hold the gathered sums in registers before the product
-// (asm below) and unroll the product by four slices, at four waves per SIMD.  Left alone, the compiler moves the
-// arithmetic of the gathers behind all of their loads, next to the stores of the sums to LDS: 130 VGPRs
-// instead of 97 at a compile-time extent, 250 with the Moebius prologue (12^3 x 24, Ls = 12, bf16:
-// M_prec 61.6 -> 41.9 us, Moebius 72.6 -> 51.6 us; FP32 63.4 -> 61.4, 16^3 x 32, Ls = 24: 303 -> 291 us).  FP16
-// interleaves the loads by hand and lost 3-10 % with it, FP64 2-10 % at Ls = 24 and 12.
-template <typename P>
-constexpr bool dense_pinned() { return std::is_same<P, P32>::value || std::is_same<P, PB16>::value; }
+// The dense-epilogue hops that hold the gathered sums in registers before the product (asm below) and
+// unroll the product by four slices, at four waves per SIMD.  Left alone, the compiler moves the arithmetic
+// of the gathers behind all of their loads, next to the stores of the sums to LDS: 130 VGPRs instead of 97
+// at a compile-time extent, 250 with the Moebius prologue (12^3 x 24, Ls = 12, bf16: M_prec 61.6 -> 41.9 us,
+// with the prologue 72.6 -> 51.6 us; FP32 63.4 -> 61.4, 16^3 x 32, Ls = 24: 303 -> 291 us).  In bf16 at run-time
+// extents without prologue it keeps them in 89 (five waves), and they lose with it (12^3 x 24, Ls = 14:
+// 51.7 -> 56.2 us).  FP16 interleaves the loads by hand and lost 3-10 %, FP64 2-10 % at Ls = 24 and 12.
+template <typename P, int LS, bool PRO>
+constexpr bool dense_pinned() {
+  return std::is_same<P, P32>::value || (std::is_same<P, PB16>::value && (PRO || LS != 0));
+}
 
 // one slice of the per-chirality matrix product along s, from a site's 12 rows in LDS (rows 6 to 11
 // off elements further)
@@ -549,11 +552,12 @@ __device__ __forceinline__ void hop_dir(const HopArgs<P>& a, const int* nb, cons
 // without an epilogue (Ls = 8, 12, 16, 32: 85, 110, 134, 253 us at 5 and at 4, 69, 72, 81, 131 us at 3); the
 // other compile-time extents spill 12 to 70 bytes at 5 and none at 3, and take 180 and 185 us (Ls = 16) and 157
 // and 176 us (Ls = 12).  Several slices per thread keep the default.
-template <typename P, int LS, int NS, bool PRO, int EPI, bool CG>
+// The dense epilogue's four waves hold but for FP32 with its links from memory, which spills 16 to 90 bytes there.
+template <typename P, int LS, int NS, bool PRO, int EPI, bool CG, bool LL>
 constexpr int hop_min_waves() {
   if (NS != 1) return 1;
   if (std::is_same<P, P16>::value) return PRO && (LS == 0 || EPI == 0) ? 3 : CG && EPI == 0 ? 4 : 5;
-  if (EPI == 1 && dense_pinned<P>()) return 4;
+  if (EPI == 1 && dense_pinned<P, LS, PRO>()) return std::is_same<P, P32>::value && !LL && !PRO ? 3 : 4;
   return 1;
 }
 
@@ -821,7 +825,7 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
       hop_dir<PAIRS ? 3 : 6, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
       hop_dir<7, DAG, PRO, NS, PAIRED>(ak, nb, L, s0, tps, pro, acc);
     }
-    if constexpr (EPI == 1 && dense_pinned<P>()) {
+    if constexpr (EPI == 1 && dense_pinned<P, LS, PRO>()) {
 #pragma unroll
       for (int j = 0; j < NS; ++j)
 #pragma unroll
@@ -864,7 +868,7 @@ __device__ __forceinline__ void hop_body(const HopArgs<P>& a, long bid, long pid
 #pragma unroll
       for (int j = 0; j < NS; ++j) {
         cx<R> o[12];
-        dense_result<R, dense_pinned<P>()>(lds + lsite * 12 * Ls, 0, s0 + j * tps, Ls, a.E, o);
+        dense_result<R, dense_pinned<P, LS, PRO>()>(lds + lsite * 12 * Ls, 0, s0 + j * tps, Ls, a.E, o);
 #pragma unroll
         for (int k = 0; k < 12; ++k) acc[j][k] = o[k];
       }
@@ -1141,7 +1145,7 @@ __global__ void __launch_bounds__(256) hop_kernel(HopArgs<P> a, int spb) {
 }
 
 template <typename P, int LS, int NS, bool DAG, bool PRO, int EPI, bool LL, bool CG, bool ST>
-__global__ void __launch_bounds__(256, (hop_min_waves<P, LS, NS, PRO, EPI, CG>())) hop_kernel(HopArgs<P> a, int spb, int xcd) {
+__global__ void __launch_bounds__(256, (hop_min_waves<P, LS, NS, PRO, EPI, CG, LL>())) hop_kernel(HopArgs<P> a, int spb, int xcd) {
   const long bid = xcd ? xcd_block(blockIdx.x, gridDim.x) : (long)blockIdx.x;
   hop_body<P, LS, NS, DAG, PRO, EPI, LL, CG, ST>(a, bid, blockIdx.x, spb);
 }
@@ -1153,7 +1157,7 @@ __global__ void __launch_bounds__(256, (hop_min_waves<P, LS, NS, PRO, EPI, CG>()
 // fields' arguments (the same kernel variant for all of them); each field's norm partials are
 // indexed by its site block.
 template <typename P, int LS, int NS, bool DAG, bool PRO, int EPI, bool LL, bool CG, bool ST>
-__global__ void __launch_bounds__(256, (hop_min_waves<P, LS, NS, PRO, EPI, CG>()))
+__global__ void __launch_bounds__(256, (hop_min_waves<P, LS, NS, PRO, EPI, CG, LL>()))
     hop_batch_kernel(const HopArgs<P>* __restrict__ args, int nrhs, int spb, int xcd) {
   const long b = xcd ? xcd_block(blockIdx.x, gridDim.x) : (long)blockIdx.x;
   const long bid = b / nrhs;
@@ -1163,7 +1167,7 @@ __global__ void __launch_bounds__(256, (hop_min_waves<P, LS, NS, PRO, EPI, CG>()
 // Right-hand sides interleaved along the fifth dimension (segments of RS slices, a.Ls = their
 // number times RS; no Moebius prologue): one slice per lane, the site's a.Ls lanes contiguous.
 template <typename P, bool DAG, int EPI, bool LL, bool CG, int RS>
-__global__ void __launch_bounds__(256, (hop_min_waves<P, 0, 1, false, EPI, CG>())) hop_ilv_kernel(HopArgs<P> a, int spb, int xcd) {
+__global__ void __launch_bounds__(256, (hop_min_waves<P, 0, 1, false, EPI, CG, LL>())) hop_ilv_kernel(HopArgs<P> a, int spb, int xcd) {
   const long bid = xcd ? xcd_block(blockIdx.x, gridDim.x) : (long)blockIdx.x;
   hop_body<P, 0, 1, DAG, false, EPI, LL, CG, false, RS>(a, bid, blockIdx.x, spb);
 }
