@@ -1136,11 +1136,9 @@ __device__ __forceinline__ void hop_split_body(const HopArgs<P>& a, long bid, in
   }
 }
 
-// (the overload of the small fields, a kernel of its own: inside the general one it raised the FP64
-// scan hops from 160 to 190 registers)
-template <typename P, int LS, int NS, bool DAG, bool PRO, int EPI, bool LL, bool CG, bool ST>
-__global__ void __launch_bounds__(256) hop_kernel(HopArgs<P> a, int spb) {
-  static_assert(NS == 1 && !ST, "small fields: one slice per lane, no staged neighbours");
+// (a kernel of its own: inside the general one it raised the FP64 scan hops from 160 to 190 registers)
+template <typename P, int LS, bool DAG, bool PRO, int EPI, bool CG>
+__global__ void __launch_bounds__(256) hop_split_kernel(HopArgs<P> a, int spb) {
   hop_split_body<P, LS, DAG, PRO, EPI, CG>(a, blockIdx.x, spb);
 }
 
@@ -1288,12 +1286,10 @@ static int launch_hop_t(const HopArgs<P>& a, const LaunchCfg& cfg, hipStream_t s
     }
   }
   if constexpr (NS == 1) {
-    constexpr bool LL = !std::is_same<P, P16>::value;
     if (split_shape<P>(cfg, a.nsites, a.Ls, PRO, DAG)) {
       const int sp = split_spb(a.Ls);
-      void (*k)(HopArgs<P>, int) = hop_kernel<P, LS, NS, DAG, PRO, EPI, LL, CG, false>;
-      hipLaunchKernelGGL(k, dim3((unsigned)((a.nsites + sp - 1) / sp)), dim3(256), 3 * 24 * 64 * sizeof(typename P::R), st,
-                         a, sp);
+      hipLaunchKernelGGL((hop_split_kernel<P, LS, DAG, PRO, EPI, CG>), dim3((unsigned)((a.nsites + sp - 1) / sp)), dim3(256),
+                         3 * 24 * 64 * sizeof(typename P::R), st, a, sp);
       return hipGetLastError() == hipSuccess ? 0 : -2;
     }
   }
@@ -1301,15 +1297,18 @@ static int launch_hop_t(const HopArgs<P>& a, const LaunchCfg& cfg, hipStream_t s
     if (stage_shape(cfg, a.Ls)) {
       LaunchCfg c2 = cfg;
       c2.ll = 1;
-      void (*k)(HopArgs<P>, int, int) = hop_kernel<P, LS, NS, DAG, PRO, EPI, true, CG, true>;
-      hipLaunchKernelGGL(k, dim3((unsigned)blocks), dim3(threads), hop_lds_bytes<P>(c2, a.Ls, false), st, a, cfg.spb, cfg.xcd);
+      hipLaunchKernelGGL((hop_kernel<P, LS, NS, DAG, PRO, EPI, true, CG, true>), dim3((unsigned)blocks), dim3(threads),
+                         hop_lds_bytes<P>(c2, a.Ls, false), st, a, cfg.spb, cfg.xcd);
       return hipGetLastError() == hipSuccess ? 0 : -2;
     }
   }
   const size_t lds = hop_lds_bytes<P>(cfg, a.Ls, EPI == 1);
-  void (*k1)(HopArgs<P>, int, int) = hop_kernel<P, LS, NS, DAG, PRO, EPI, true, CG, false>;
-  void (*k0)(HopArgs<P>, int, int) = hop_kernel<P, LS, NS, DAG, PRO, EPI, false, CG, false>;
-  hipLaunchKernelGGL(cfg.ll ? k1 : k0, dim3((unsigned)blocks), dim3(threads), lds, st, a, cfg.spb, cfg.xcd);
+  if (cfg.ll)
+    hipLaunchKernelGGL((hop_kernel<P, LS, NS, DAG, PRO, EPI, true, CG, false>), dim3((unsigned)blocks), dim3(threads), lds,
+                       st, a, cfg.spb, cfg.xcd);
+  else
+    hipLaunchKernelGGL((hop_kernel<P, LS, NS, DAG, PRO, EPI, false, CG, false>), dim3((unsigned)blocks), dim3(threads), lds,
+                       st, a, cfg.spb, cfg.xcd);
   return hipGetLastError() == hipSuccess ? 0 : -2;
 }
 

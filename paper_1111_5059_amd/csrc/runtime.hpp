@@ -324,6 +324,9 @@ struct Op {
     const int ls = (Ls == 8 || Ls == 12 || Ls == 16 || Ls == 32) ? Ls : 0;
     int epi = 0;
     if (a.E) epi = (a.epi_scan && cfg.ns == 1 && (ls == 8 || ls == 16 || ls == 32)) ? (a.out2.data ? 3 : 2) : 1;
+    if (!batch && split_shape<P>(cfg, a.nsites, Ls, pro, dag))
+      return std::string("hop_split_kernel<") + prec_tag(P::ID) + ", " + std::to_string(ls) + ", " + (dag ? "true" : "false") +
+             ", " + (pro ? "true" : "false") + ", " + std::to_string(epi) + ", " + (a.cg_r.data ? "true" : "false") + ">";
     const bool st = !batch && P::ID == DWF_FP16 && cfg.ns == 1 && !pro && epi != 1 &&
                     (ls == 8 || ls == 16 || ls == 32) && stage_shape(cfg, Ls);
     return std::string(batch ? "hop_batch_kernel<" : "hop_kernel<") + prec_tag(P::ID) + ", " + std::to_string(ls) +

@@ -228,6 +228,86 @@ def test_batched_ladder_at_Ls16(env, ora, prec):
         assert np.linalg.norm(r) <= 1.05e-10 * np.linalg.norm(srcs[k]), (k, m)
 
 
+# ------------------------------------------------------------------ the kernels of large fields
+# The lattices above are small enough for the default shapes to spread a hop's directions over the waves
+# of a workgroup (hop_split_kernel).  The benchmark's fields take the general kernel: the same comparisons
+# with the default shapes set explicitly, which the library uses at every size.
+@pytest.fixture
+def large_field_kernels(env):
+    dwf, ctx = env
+    keys = [(P, Ls) for P in range(4) for Ls in (16, 32)]
+    for P, Ls in keys:
+        dwf.dwf_tune_set(ctx, P, Ls, *dwf.dwf_tune_get(ctx, P, Ls))
+    yield env
+    for P, Ls in keys:
+        dwf.dwf_tune_set(ctx, P, Ls, 0, 0)
+
+
+@pytest.mark.parametrize("Ls,b,c,m", SYSTEMS)
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16"])
+def test_cg_ne_with_the_kernels_of_large_fields(large_field_kernels, ora, Ls, b, c, m, prec):
+    test_cg_ne_at_bench_extents(large_field_kernels, ora, Ls, b, c, m, prec)
+
+
+@pytest.mark.parametrize("Ls,b,c,m", SYSTEMS)
+def test_partial_cg_iterates_with_the_kernels_of_large_fields(large_field_kernels, ora, Ls, b, c, m):
+    test_partial_cg_iterates_at_bench_extents(large_field_kernels, ora, Ls, b, c, m, 3)
+    for prec in ("fp32", "fp16", "bf16"):
+        test_partial_cg_iterates_low_precision(large_field_kernels, ora, Ls, b, c, m, prec)
+
+
+@pytest.mark.parametrize("b,c,m", [(1.0, 0.0, 0.005), (1.5, 0.5, 0.005), (1.0, 0.0, 1.0)])
+def test_fp64_operators_with_the_kernels_of_large_fields(large_field_kernels, ora, b, c, m):
+    test_fp64_operators_at_Ls32(large_field_kernels, ora, b, c, m)
+
+
+def test_madwf_with_the_kernels_of_large_fields(large_field_kernels, ora):
+    test_madwf_at_bench_settings(large_field_kernels, ora)
+
+
+# instances that the solve launches only on fields as large as the benchmark's: the FP64 residuals of the
+# Moebius system with the input factor in a pass, their first hop plain
+LARGE_ONLY_KERNELS = {
+    "hop_kernel<dwf::P64, 16, 1, false, false, 2, true, false, false>",
+    "fifth_kernel<dwf::P64, 16>",
+}
+LAUNCHED_LARGE = set()
+
+
+@pytest.mark.parametrize("prec,dims", [("fp64", (8, 8, 8, 18)), ("fp64", (8, 8, 16, 32)), ("fp32", (8, 8, 8, 34))])
+def test_moebius_operators_on_larger_fields(env, ora, prec, dims):
+    """M_prec, its adjoint, D and D^dag of the Ls' = 16 Moebius operator at default shapes on fields that take
+    the general kernel and M_prec's input factor in a pass (FP64 above 65536 5D sites, FP32 above
+    131072; the second lattice also streams its operands), against the oracle."""
+    dwf, ctx = env
+    P, Ls, m = dwf.PREC_NAMES[prec], 16, 0.005
+    U = synth.random_links(dims, 0.6, 63)
+    psi = synth.gaussian_spinor(dims, Ls, 64)
+    lat = dwf.Lattice(ctx, dims, Ls, M5=1.8, mass=m, b=1.5, c=0.5)
+    po = ora.params(dims, Ls, M5=1.8, mass=m, b=1.5, c=0.5)
+    Ug, p = lat.pack_gauge(U, P), lat.params(P)
+    psio = mask(psi, dims, 1)
+    full, odd = lat.pack(psi, dwf.KIND_FULL, P), lat.pack(psio, dwf.KIND_ODD, P)
+    dwf.dwf_timing_report(ctx)
+    for dag in (False, True):
+        dst = lat.empty(dwf.KIND_FULL, P)
+        dwf.mobius_dslash(ctx, p, Ug, full, dst, dwf.OP_FULL, 0, dag)
+        assert rel_err(lat.unpack_np(dst, dwf.KIND_FULL, P), ora.dwf(po, U, psi, dagger=dag)) < PREC_TOL[prec], ("D", dag)
+        dst = lat.empty(dwf.KIND_ODD, P)
+        dwf.mobius_dslash(ctx, p, Ug, odd, dst, dwf.OP_MPREC, 1, dag)
+        err = rel_err(lat.unpack_np(dst, dwf.KIND_ODD, P), ora.mprec(po, U, psio, dagger=dag))
+        assert err < PREC_TOL[prec], ("M", dag)
+    rep = dwf.dwf_timing_report(ctx)
+    assert not any("split" in k for k in rep), rep
+    LAUNCHED_LARGE.update(rep)
+
+
+def test_every_large_only_kernel_was_checked():
+    if not LAUNCHED_LARGE:
+        pytest.skip("needs the larger fields' test to run first")
+    assert LARGE_ONLY_KERNELS <= LAUNCHED_LARGE, sorted(LARGE_ONLY_KERNELS - LAUNCHED_LARGE)
+
+
 def test_every_bench_kernel_was_checked():
     """Runs after the tests above (same module, file order): every kernel instance of the
     benchmark step was launched by at least one of them."""

@@ -392,3 +392,34 @@ def test_5d_hop_reads_neighbouring_slices_only(env, prec, shape):
             assert np.isfinite(out[0]).all() and np.array_equal(out[0], out[1]), dag
     finally:
         dwf.dwf_tune_set(ctx, P, Ls, 0, 0)
+
+
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "fp16", "bf16"])
+def test_timer_names_the_small_field_kernel(env, prec):
+    """The report names the kernel that ran: hop_split_kernel at the default shape of a small field,
+    hop_kernel with a shape set explicitly and on a larger field."""
+    dwf, ctx = env
+    P, Ls, tag = dwf.PREC_NAMES[prec], 16, {"fp64": "P64", "fp32": "P32", "fp16": "P16", "bf16": "PB16"}[prec]
+
+    def names(dims):
+        lat = dwf.Lattice(ctx, dims, Ls, mass=0.2)
+        Ug, p = lat.pack_gauge(synth.random_links(dims, 0.5, 970), P), lat.params(P)
+        src, dst = lat.pack(synth.gaussian_spinor(dims, Ls, 971), dwf.KIND_ODD, P), lat.empty(dwf.KIND_ODD, P)
+        dwf.dwf_timing_report(ctx)
+        dwf.dwf_timing_enable(ctx, True)
+        try:
+            dwf.dwf_dslash(ctx, p, Ug, src, dst, dwf.OP_MPREC, 1, False)
+            return dwf.dwf_timing_report(ctx)
+        finally:
+            dwf.dwf_timing_enable(ctx, False)
+
+    small = names((4, 4, 4, 4))
+    assert set(small) == {f"hop_split_kernel<dwf::{tag}, 16, false, false, 2, false>"}
+    assert next(iter(small.values()))["launches"] == 2
+    general = {f"hop_kernel<dwf::{tag}, 16, 1, false, false, 2, {'false' if prec == 'fp16' else 'true'}, false, false>"}
+    assert set(names((8, 8, 8, 24))) == general
+    dwf.dwf_tune_set(ctx, P, Ls, *dwf.dwf_tune_get(ctx, P, Ls))
+    try:
+        assert set(names((4, 4, 4, 4))) == general
+    finally:
+        dwf.dwf_tune_set(ctx, P, Ls, 0, 0)
