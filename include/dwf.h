@@ -334,7 +334,7 @@ int dwf_tune_get(dwf_ctx* ctx, int kernel_id, int prec, int Ls, int* sites_per_b
  * extent (DWF_ERR_ARG otherwise); 0, 0, 0 restores the default: among the tiles of at most
  * 600 sites per t-slice, the one with the smallest halo ratio (tx+2)(ty+2)(tz+2)/(tx ty tz).
  * dwf_tune_tile waits for the context stream before it replaces the order; tile is an int[3]
- * host array. */
+ * host array.  Small fields at the default launch shape (see dwf_tune_set) do not read it. */
 int dwf_tune_tile(dwf_ctx* ctx, const int* dims, int tbc, const int* tile);
 int dwf_tune_tile_get(dwf_ctx* ctx, const int* dims, int tbc, int* tile);
 

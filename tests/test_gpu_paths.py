@@ -423,3 +423,62 @@ def test_timer_names_the_small_field_kernel(env, prec):
         assert set(names((4, 4, 4, 4))) == general
     finally:
         dwf.dwf_tune_set(ctx, P, Ls, 0, 0)
+
+
+@pytest.mark.parametrize("Ls,spb,ns", [(7, 18, 1), (16, 8, 1), (16, 8, 2), (32, 4, 4)])
+@pytest.mark.parametrize("prec", ["fp64", "fp32", "bf16"])
+@pytest.mark.parametrize("kind", ["shamir", "moebius", "sdep"])
+def test_full_operator_in_the_general_kernel(env, ora, Ls, spb, ns, prec, kind):
+    """D and D^dag with A on the axpy operand in the kernel that larger fields take, one and several
+    slices per thread, against the oracle."""
+    dwf, ctx = env
+    P, dims = dwf.PREC_NAMES[prec], (4, 2, 6, 4)
+    kw, okw = {}, {}
+    if kind == "moebius":
+        kw = okw = {"b": 1.5, "c": 0.5}
+    elif kind == "sdep":
+        w = 1.5 + 0.5 * np.sin(np.arange(Ls))
+        kw = {"b_s": (w + 1) / 2, "c_s": (w - 1) / 2}
+        okw = {"bs": kw["b_s"], "cs": kw["c_s"]}
+    U = synth.random_links(dims, 0.5, 980)
+    psi = synth.gaussian_spinor(dims, Ls, 981 + Ls)
+    lat = dwf.Lattice(ctx, dims, Ls, mass=0.2, tbc=1, **kw)
+    po = ora.params(dims, Ls, mass=0.2, tbc=1, **okw)
+    Ug, p, src = lat.pack_gauge(U, P), lat.params(P), lat.pack(psi, dwf.KIND_FULL, P)
+    dwf.dwf_tune_set(ctx, P, Ls, spb, ns)
+    try:
+        for dag in (False, True):
+            dst = lat.empty(dwf.KIND_FULL, P)
+            dwf.mobius_dslash(ctx, p, Ug, src, dst, dwf.OP_FULL, 0, dag)
+            err = rel_err(lat.unpack_np(dst, dwf.KIND_FULL, P), ora.dwf(po, U, psi, dagger=dag))
+            assert err < PREC_TOL[prec], (dag, err)
+    finally:
+        dwf.dwf_tune_set(ctx, P, Ls, 0, 0)
+
+
+def test_traversal_tile_in_the_general_kernel(env, ora):
+    """Every traversal tile gives bit-identical M_prec and M_prec^dag that agree with the oracle, in the
+    kernel that reads the order (a shape set explicitly: small fields at the default shape do not)."""
+    dwf, ctx = env
+    P, dims, Ls = dwf.FP32, (12, 4, 6, 8), 8
+    U = synth.random_links(dims, 0.5, 990)
+    psio = mask(synth.gaussian_spinor(dims, Ls, 991), dims, 1)
+    lat = dwf.Lattice(ctx, dims, Ls, mass=0.05, b=1.5, c=0.5, tbc=1)
+    Ug, src = lat.pack_gauge(U, P), lat.pack(psio, dwf.KIND_ODD, P)
+    po = ora.params(dims, Ls, mass=0.05, b=1.5, c=0.5, tbc=1)
+    dwf.dwf_tune_set(ctx, P, Ls, *dwf.dwf_tune_get(ctx, P, Ls))
+    try:
+        first = {}
+        for tile in [(0, 0, 0), (2, 2, 2), (12, 4, 6), (4, 2, 3), (6, 4, 2), (3, 1, 1)]:
+            dwf.dwf_tune_tile(ctx, dims, tile, 1)
+            for dag in (False, True):
+                dst = lat.empty(dwf.KIND_ODD, P)
+                dwf.mobius_dslash(ctx, lat.params(P), Ug, src, dst, dwf.OP_MPREC, 1, dag)
+                got = lat.unpack_np(dst, dwf.KIND_ODD, P)
+                if dag not in first:
+                    first[dag] = got
+                    assert rel_err(got, ora.mprec(po, U, psio, dagger=dag)) < PREC_TOL["fp32"]
+                assert np.array_equal(got, first[dag]), (tile, dag)
+    finally:
+        dwf.dwf_tune_tile(ctx, dims, (0, 0, 0), 1)
+        dwf.dwf_tune_set(ctx, P, Ls, 0, 0)
