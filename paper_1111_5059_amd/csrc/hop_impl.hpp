@@ -128,14 +128,15 @@ struct MfmaTile<double> {  // D[l / 16 + 4 r][l % 16]
 // the same product was not faster (FP32 Ls = 16 M_prec 236 -> 243 us, FP64 Ls = 24 542 -> 619 us): the registers it
 // holds across its two barriers cost more than the reads it saves.  Extents beyond 32 would need more
 // accumulators than that: one lane per slice.
-// Where the padding to 4 slices and 16 outputs leaves too little of a tile in use, the lanes' own product
-// is not slower (16^3 x 32, before and after: FP64 Ls = 7 35.4, 35.1, 8 47.8, 36.1, 16 106, 80, 32 220,
-// 160 us; FP32 Ls = 10 23.2, 25.9, 12 28.7, 27.5, 16 36.4, 33.8, 18 42.7, 48.5, 20 54.0, 50.7, 32 159, 100 us;
-// FP16 Ls = 12 28.7, 23.8, 13 27.7, 29.0, 15 32.6, 30.2, 30 85, 73 us).
-template <typename R>
+// Where the lanes' own product was not slower it stays: in FP32 arithmetic where the padding to 4 slices
+// and 16 outputs leaves too little of a tile in use, and in 16-bit storage, which hides less behind its
+// loads, below 24 (16^3 x 32, lanes / matrix cores: FP64 Ls = 7 35.4, 35.1, 8 47.8, 36.1, 16 106, 80, 32 220, 160 us;
+// FP32 Ls = 10 23.2, 25.9, 12 28.7, 27.5, 16 36.4, 33.8, 18 42.7, 48.5, 20 54.0, 50.7, 32 159, 100 us; FP16 Ls = 12
+// 28.7, 23.8, 13 27.7, 29.0, 15 32.6, 30.2, 30 85, 73 us; 12^3 x 24, Ls = 20, bf16 19.4, 20.4 us).
+template <typename P>
 __device__ __forceinline__ bool dense_mfma_shape(int Ls) {
-  if (sizeof(R) == 8) return Ls >= 8 && Ls <= 32;
-  return Ls == 12 || Ls == 15 || Ls == 16 || (Ls >= 20 && Ls <= 32);
+  if (sizeof(typename P::R) == 8) return Ls >= 8 && Ls <= 32;
+  return Ls == 12 || Ls == 15 || Ls == 16 || (Ls >= (sizeof(typename P::S) == 8 ? 20 : 24) && Ls <= 32);
 }
 template <typename R, int KK, int NT>
 __device__ __forceinline__ void dense_tiles(cx<R>* rows, const DenseRows& d, const R* E) {
@@ -1454,7 +1455,7 @@ __global__ void __launch_bounds__(256, (LSEG == 0 && sizeof(typename P::R) == 4 
     return;
   }
   const DenseRows d(Ls, spb);
-  const bool mfma = dense_mfma_shape<R>(Ls);
+  const bool mfma = dense_mfma_shape<P>(Ls);
   if (active) {
     cx<R> v[12];
     load_spinor<P>(in, x, s, Ls, v);
