@@ -808,9 +808,9 @@ int launch_pack_full(const GeomTables& g, int Ls, const double2* natural, Half<P
   // with a last tile of one to four slices, whose lines two workgroups write in parts (16^3 x 32, tiles /
   // halves: FP64 Ls = 17 260 / 216 us, Ls = 33 600 / 428 us, FP32 Ls = 20 232 / 199 us, Ls = 24 208 / 235 us), and FP16, whose
   // norms keep few of a tile's threads busy, at two and three slices and beyond 32 (Ls = 3 26.7 / 23.8 us, Ls = 33
-  // 378 / 316 us, Ls = 17 153 / 157 us).
+  // 378 / 316 us, Ls = 17 153 / 157 us).  Small fields are packed in one launch.
   const int rest = Ls % TILE_L;
-  if (P::NORM ? Ls < 4 || Ls > 32 : sizeof(typename P::S) >= 8 && Ls > TILE_L && rest >= 1 && rest <= 4) {
+  if (g.V * Ls >= 262144 && (P::NORM ? Ls < 4 || Ls > 32 : sizeof(typename P::S) >= 8 && Ls > TILE_L && rest >= 1 && rest <= 4)) {
     const int rc = launch_pack_half<P>(g, 0, Ls, natural, even, st);
     return rc != 0 ? rc : launch_pack_half<P>(g, 1, Ls, natural, odd, st);
   }
