@@ -1367,8 +1367,11 @@ static void force_terms(dwf_ctx* ctx, const Op<P64>& op, const void* Unat, CHalf
   Half<P64> Xe = hview<P64>(ws_get(ctx, "force.Xe", hb), g, Ls);
   Half<P64> Zo = hview<P64>(ws_get(ctx, "force.Zo", hb), g, Ls);
   Half<P64> Ze = hview<P64>(ws_get(ctx, "force.Ze", hb), g, Ls);
-  Half<P64> We = hview<P64>(ws_get(ctx, "force.We", hb), g, Ls);
-  Half<P64> Wo = hview<P64>(ws_get(ctx, "force.Wo", hb), g, Ls);
+  Half<P64> We = {nullptr, nullptr}, Wo = {nullptr, nullptr};
+  if (op.moebius) {
+    We = hview<P64>(ws_get(ctx, "force.We", hb), g, Ls);
+    Wo = hview<P64>(ws_get(ctx, "force.Wo", hb), g, Ls);
+  }
   // W_o = F X, X_e = A^-1 B_eo X = -1/2 A^-1 H W_o, W_e = F X_e (Shamir: F = 1)
   if (op.moebius) op.fifth(X, Wo, E_F);
   const CHalf<P64> wo = op.moebius ? cv(Wo) : X;
