@@ -3,9 +3,12 @@
 For one (precision, Ls, lattice) it times the even-odd operator M_prec (the solver's inner
 kernel mix: hops with the fused fifth-dimension epilogue, prologue and axpy) over every valid
 launch shape -- 4D sites per workgroup, s-slices per thread, XCD-aware workgroup order, links
-or neighbour spinors staged in LDS -- keeps the fastest, installs it with ``dwf_tune_set`` and caches it in a JSON
-file keyed by (kernel, precision, Ls, lattice).  Shapes the kernel cannot run (more than 256
-threads, LDS above 64 KiB) are never tried: the library rejects them before launching.
+or neighbour spinors staged in LDS -- and the library's default, keeps the fastest, installs it with
+``dwf_tune_set`` and caches it in a JSON file keyed by (kernel, precision, Ls, lattice).  Shapes the
+kernel cannot run (more than 256 threads, LDS above 64 KiB) are never tried: the library rejects them
+before launching.  An installed shape holds for every lattice of the context at that precision and Ls
+(``load`` installs another lattice's entry); the default, which on small fields is a kernel that no
+shape selects, is an entry of zeros.
 
 ``tune_tile`` searches the traversal tile of a lattice the same way (``dwf_tune_tile``): the
 3D tile of spatial sites the workgroups walk along t, which sets how much of each input
@@ -22,6 +25,7 @@ import os
 from . import (FP64, KIND_FULL, KIND_GAUGE, KIND_ODD, OP_MPREC, PREC_NAMES, DwfError, cg_ne_batched, dwf_convert,
                dwf_dslash, dwf_tune_get, dwf_tune_set, dwf_tune_tile, dwf_tune_tile_get)
 
+DEFAULT_SHAPE = {"spb": 0, "ns": 0, "xcd": 0, "ll": 0}  # dwf_tune_set: the library's own choice
 DEFAULT_CACHE = os.path.join(os.path.expanduser("~"), ".cache", "dwf_mi355x_tune.json")
 
 
@@ -66,12 +70,13 @@ def _time_mprec(lattice, Ug, src, dst, p, reps):
 
 
 def tune_hop(lattice, U64, prec, reps=5, cache=DEFAULT_CACHE, shapes=None, verbose=False):
-    """Search the launch shapes for ``prec`` on ``lattice``; returns (best shape, ms, table)."""
+    """Search the launch shapes (default: all of them and the library's own choice, DEFAULT_SHAPE) for
+    ``prec`` on ``lattice``; returns (best shape, ms, table)."""
     P = PREC_NAMES.get(prec, prec)
     p, Ug, src, dst = _operands(lattice, U64, P)
     table = []
     best = None
-    for c in shapes or candidates(P, lattice.Ls):
+    for c in shapes or [DEFAULT_SHAPE] + candidates(P, lattice.Ls):
         try:
             dwf_tune_set(lattice.ctx, P, lattice.Ls, c["spb"], c["ns"], c["xcd"], c["ll"])
         except DwfError:

@@ -482,3 +482,29 @@ def test_traversal_tile_in_the_general_kernel(env, ora):
     finally:
         dwf.dwf_tune_tile(ctx, dims, (0, 0, 0), 1)
         dwf.dwf_tune_set(ctx, P, Ls, 0, 0)
+
+
+def test_autotuner_keeps_the_default_where_it_is_faster(env, tmp_path, monkeypatch):
+    """The search times the library's own choice beside the explicit shapes and installs and caches it where
+    it wins: on a small field it is a kernel that no explicit shape selects."""
+    from paper_1111_5059_amd import autotune
+    dwf, ctx = env
+    dims, Ls, P = (4, 4, 4, 4), 16, dwf.FP32
+    lat = dwf.Lattice(ctx, dims, Ls, mass=0.05)
+    U64 = lat.pack_gauge(synth.random_links(dims, 0.5, 995))
+    cache = str(tmp_path / "tune.json")
+    monkeypatch.setattr(autotune, "candidates", lambda P, Ls: [{"spb": 1, "ns": 1, "xcd": 0, "ll": 0}])
+    try:
+        best, ms, table = autotune.tune_hop(lat, U64, "fp32", reps=20, cache=cache)
+        assert best == autotune.DEFAULT_SHAPE and len(table) == 2 and ms == min(r["ms"] for r in table)
+        dwf.dwf_tune_set(ctx, P, Ls, 1, 1)
+        assert autotune.load(lat, "fp32", cache) == dict(best, ms=ms)
+        src, dst = lat.zeros(dwf.KIND_ODD, P), lat.empty(dwf.KIND_ODD, P)
+        Ug = lat.pack_gauge(synth.random_links(dims, 0.5, 995), P)
+        dwf.dwf_timing_report(ctx)
+        dwf.dwf_timing_enable(ctx, True)
+        dwf.dwf_dslash(ctx, lat.params(P), Ug, src, dst, dwf.OP_MPREC, 1, False)
+        assert all(k.startswith("hop_split_kernel<") for k in dwf.dwf_timing_report(ctx))
+    finally:
+        dwf.dwf_timing_enable(ctx, False)
+        dwf.dwf_tune_set(ctx, P, Ls, 0, 0)
