@@ -191,6 +191,9 @@ int dwf_ctx_create(dwf_ctx** out, void* stream) {
     std::unique_ptr<dwf_ctx> c(new dwf_ctx());  // (freed if a step below fails)
     c->stream = reinterpret_cast<hipStream_t>(stream);
     DWF_CHECK_HIP(hipGetDevice(&c->device));
+    unsigned flags = 0;
+    DWF_CHECK_HIP(hipGetDeviceFlags(&flags));
+    c->blocking = (flags & hipDeviceScheduleMask) == hipDeviceScheduleBlockingSync;
     scratch_init();  // device address of the no-allocation entry point's array on this device
     DWF_CHECK_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->h_scalars), S_COUNT * sizeof(double)));
     DWF_CHECK_HIP(hipHostMalloc(reinterpret_cast<void**>(&c->h_poll), HOST_POLL * sizeof(double),

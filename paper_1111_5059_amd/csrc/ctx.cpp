@@ -43,6 +43,8 @@ void arm_host(dwf_ctx* ctx, int n) {
 
 double wait_host(dwf_ctx* ctx, int k) {
   const volatile uint64_t* p = reinterpret_cast<const volatile uint64_t*>(ctx->h_poll) + k;
+  // (a caller that chose blocking waits for its device gets one here too)
+  if (ctx->blocking) DWF_CHECK_HIP(hipStreamSynchronize(ctx->stream));
   uint64_t v = *p;
   for (long n = 1; v == UNWRITTEN; ++n) {
     if ((n & 0xfff) == 0) {  // a few tens of microseconds: has the stream ended, or failed?

@@ -87,6 +87,7 @@ struct KernelTimer {
 struct dwf_ctx {
   hipStream_t stream = nullptr;
   int device = 0;
+  bool blocking = false;  // the device was set to blocking waits (hipDeviceScheduleBlockingSync)
   std::map<std::string, std::pair<void*, size_t>> ws;
   std::vector<std::unique_ptr<dwf::Geometry>> geoms;
   std::map<std::string, std::pair<void*, size_t>> emats;  // fifth-dimension matrices by key

@@ -508,3 +508,35 @@ def test_autotuner_keeps_the_default_where_it_is_faster(env, tmp_path, monkeypat
     finally:
         dwf.dwf_timing_enable(ctx, False)
         dwf.dwf_tune_set(ctx, P, Ls, 0, 0)
+
+
+BLOCKING_SOLVE = """
+import ctypes, time
+assert ctypes.CDLL("libamdhip64.so").hipSetDeviceFlags(4) == 0  # hipDeviceScheduleBlockingSync
+import torch, paper_1111_5059_amd as dwf
+ctx = dwf.Context()
+lat = dwf.Lattice(ctx, (24, 24, 24, 24), 16, mass=0.01)
+b, x = lat.empty(dwf.KIND_FULL), lat.zeros(dwf.KIND_FULL)
+b.view(torch.float64).normal_()
+U = lat.empty(dwf.KIND_GAUGE)
+U.view(torch.float64).normal_(std=0.3)
+dwf.cg_ne(ctx, lat.params(), U, b, x, tol=1e-14, maxit=2)
+x.zero_()
+torch.cuda.synchronize()
+c, w = time.process_time(), time.perf_counter()
+dwf.cg_ne(ctx, lat.params(), U, b, x, tol=1e-14, maxit=100)
+print("share", (time.process_time() - c) / (time.perf_counter() - w))
+"""
+
+
+def test_blocking_device_schedule_is_kept():
+    """A program that set its device to blocking waits is not kept busy by a solve whose iterations take
+    milliseconds (a wait that spins uses a whole core, and the threads of the runtime a little more)."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", BLOCKING_SOLVE], capture_output=True, text=True, timeout=100, cwd=root,
+                       env=dict(os.environ, PYTHONPATH=root))
+    assert r.returncode == 0, r.stderr[-2000:]
+    assert float(r.stdout.split("share")[1]) < 0.6, r.stdout
