@@ -308,7 +308,7 @@ struct FifthScan {
 // (32 lanes: with ds_bpermute) and multiplies and adds them.
 // Moving every value with ds_bpermute and selecting took 144 of them and about 340 VALU instructions per
 // lane in FP32: the FP16 hops with this epilogue at 24^3 x 64, Ls = 32 went from 676 to 599 us, those with
-// two of them from 920 to 752 us; M_prec in FP64, Ls = 16 at 16^3 x 32 340 -> 297 us (DPP and the rest of that
+// two of them from 920 to 752 us; M_prec in FP64, Ls = 16 at 16^3 x 32 344 -> 301 us (DPP and the rest of that
 // hop's changes), A^-1 in FP32, Ls = 8 at 12^3 x 24 7.7 -> 5.7 us.
 // Rotations with the boundary's factor -m in the wrapped lanes need no closing step, but round every
 // lane in every step and the common factor 1 / (1 + m a^LSEG) once more: FP32 A^-1 at Ls = 8 was 1.38 times as
